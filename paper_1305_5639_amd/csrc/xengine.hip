@@ -15,7 +15,8 @@
 // one channel's triangle, TILE = 64 or 128.  Its waves form a 2 x (TILE / 32)
 // grid: each wave owns TILE / 2 rows and one 32-column block, as 32x32 MFMA
 // blocks with separate real and imaginary accumulators (TILE = 128: 8 waves of
-// 64 x 32, 512 threads; TILE = 64: 4 waves of 32 x 32).  On diagonal blocks
+// 64 x 32, 512 threads, for FP32 4 waves of 64 x 64; TILE = 64: 4 waves of 32 x
+// 32).  FP32 is summed as three BF16 parts (below).  On diagonal blocks
 // the waves whose columns lie wholly right of their rows idle, and a wave
 // whose first 32 rows do skips that row block.  The K loop walks time blocks
 // through a two-slot LDS ring filled by direct global-to-LDS copies
@@ -23,8 +24,8 @@
 // (both planes) of each operand, with each row's 16-byte chunks XOR-swizzled
 // so that 16 consecutive rows cover all 64 LDS banks.  Every lane reads 32
 // bytes per (row block, plane) per stage, which is one K step for FP8
-// (32x32x64), two for int8 (32x32x32) and FP16 (32x32x16), and eight for FP32
-// (32x32x2).  Because the same K assignment is used for both operands, the
+// (32x32x64), two for int8 (32x32x32) and FP16 (32x32x16), one per pair of parts
+// for FP32 (32x32x16).  Because the same K assignment is used for both operands, the
 // spectrum-to-slot order inside a stage does not matter.
 //
 // Workgroups map XCD-major (each XCD takes a contiguous range of
@@ -156,73 +157,205 @@ template <int NT> struct XT<P_FP8, NT> {
     }
 };
 
-// Wave layout of a TILE x TILE block: 2 x WC waves, each owning QS = TILE / 2
-// rows (FR blocks of 32) and one 32-column block.  TILE = 128: 8 waves of
-// 64 x 32; TILE = 64: 4 waves of 32 x 32.  Narrow waves keep the complex
-// accumulators of a wave at 32 FR registers each for Re and Im, so four waves
-// share each SIMD: while some wait at a barrier or on LDS, others issue MFMAs.
-template <int TILE> struct WaveGrid {
-    static constexpr int WC = TILE / 32;               // waves across the columns
-    static constexpr int NW = 2 * WC;                  // waves
-    static constexpr int THREADS = 64 * NW;
+// Wave layout of a TILE x TILE block: WR x WC waves, each owning QS rows (FR
+// blocks of 32) and QC columns (FC blocks of 32).  The FP16, FP8 and int8
+// forms take narrow waves, 64 x 32 (TILE = 128, 8 waves) or 32 x 32 (TILE =
+// 64, 4 waves): their complex accumulators fit 64 registers, so four waves
+// share each SIMD, and while some wait at a barrier or on LDS the others issue
+// MFMAs.  FP32 with TILE = 128 takes 4 waves of 64 x 64, two per SIMD: its
+// fragments are split on the vector ALU after the LDS read, and a wave of
+// twice the columns splits each row half as often.
+template <int PREC, int TILE> struct WaveGrid {
     static constexpr int FR = TILE / 64;               // 32-row blocks per wave
-    static constexpr int QS = TILE / 2;                // rows per wave
+    static constexpr int FC = PREC == P_FP32 ? TILE / 64 : 1;   // 32-column blocks per wave
+    static constexpr int QS = 32 * FR;                 // rows per wave
+    static constexpr int QC = 32 * FC;                 // columns per wave
+    static constexpr int WC = TILE / QC;               // waves across the columns
+    static constexpr int NW = TILE / QS * WC;          // waves
+    static constexpr int THREADS = 64 * NW;
+    static constexpr int EU = FR * FC > 2 ? 2 : 4;     // waves per SIMD
 };
 
-// One stage of a wave's FR blocks of 32x32.  pa / pb point at the lane's row
-// (row block 0) and column in the stage; off[plane][t] are the lane's
-// swizzled chunk offsets in a row.  Four real products per block (Re += Ar Br
-// + Ai Bi, Im += Ar Bi + Ai (-Br)).  The column fragment is read once, each
-// row block's fragments just before its MFMAs, and (except for FP8, whose
-// MFMA takes both chunks) one 16-byte chunk at a time, which keeps the live
-// fragment registers few enough for four waves per SIMD.  SKIP = 1: a
-// diagonal wave whose first row block lies wholly above the diagonal leaves
-// it out; SKIP = 2: a wave whose last row block lies wholly past the inputs
-// leaves that out.
-template <int PREC, int FR, int SKIP, typename Acc>
-__device__ __forceinline__ void wave_stage(Acc (&re)[FR], Acc (&im)[FR], const uint8_t *pa, const uint8_t *pb,
-                                           const int (&off)[2][kNT]) {
+// Row blocks a wave one block wide leaves out: SKIP = 1, a diagonal wave's first,
+// lying wholly above the diagonal; SKIP = 2, a last one wholly past the inputs.
+// (In waves two blocks wide the branch costs more registers than there are.)
+template <int FR, int SKIP> constexpr bool skipped(int f) {
+    return (SKIP == 1 && f == 0) || (SKIP == 2 && f == FR - 1);
+}
+
+// One stage of a wave's FR x FC blocks of 32x32.  pa / pb point at the lane's
+// row (row block 0) and column (column block 0) in the stage; off[plane][t]
+// are the lane's swizzled chunk offsets in a row.  Four real products per
+// block (Re += Ar Br + Ai Bi, Im += Ar Bi + Ai (-Br)).  The column fragments
+// are read once, each row block's fragments just before its MFMAs, and
+// (except for FP8, whose MFMA takes both chunks) one 16-byte chunk at a time,
+// which keeps the live fragment registers few enough for four waves per SIMD.
+template <int PREC, int FR, int FC, int SKIP, typename Acc>
+__device__ __forceinline__ void wave_stage(Acc (&re)[FR][FC], Acc (&im)[FR][FC], const uint8_t *pa,
+                                           const uint8_t *pb, const int (&off)[2][kNT]) {
     constexpr int NC = PREC == P_FP8 ? 1 : kNT;        // chunk groups per stage
     constexpr int NTC = kNT / NC;                      // chunks per fragment
     using X = XT<PREC, NTC>;
     // The compiler's MFMA / LDS-read interleaving strategies, chosen per form
     // by measurement: FP16 at 1024 x 4096 x 1024 17.27 -> 16.54 ms and at 512 x
     // 2048 x 2048 4.24 -> 4.14 ms (strategy 0); int8 at 512 x 2048 x 2048
-    // 2.44 -> 2.38 ms and FP32 133.5 -> 132.8 ms (strategy 1).  FP8, whose
-    // fragments take both chunks at once, spills under either and keeps none.
+    // 2.44 -> 2.38 ms (strategy 1).  FP8, whose fragments take both chunks at
+    // once, spills under either and keeps none.
     if constexpr (PREC == P_FP16) __builtin_amdgcn_iglp_opt(0);
-    else if constexpr (PREC == P_FP32 || PREC == P_INT8) __builtin_amdgcn_iglp_opt(1);
+    else if constexpr (PREC == P_INT8) __builtin_amdgcn_iglp_opt(1);
 #pragma unroll
     for (int t = 0; t < NC; ++t) {
-        const typename X::Frag b0 = X::load(pb, off[0] + t * NTC);
-        const typename X::Frag b1 = X::load(pb, off[1] + t * NTC);
-        const typename X::Frag nb = X::neg(b0);
+        typename X::Frag b0[FC], b1[FC], nb[FC];
+#pragma unroll
+        for (int c = 0; c < FC; ++c) {
+            b0[c] = X::load(pb + c * 32 * kRB, off[0] + t * NTC);
+            b1[c] = X::load(pb + c * 32 * kRB, off[1] + t * NTC);
+            nb[c] = X::neg(b0[c]);
+        }
 #pragma unroll
         for (int f = 0; f < FR; ++f) {
-            if ((SKIP == 1 && f == 0) || (SKIP == 2 && f == FR - 1)) continue;
+            if (skipped<FR, SKIP>(f)) continue;
             const typename X::Frag a0 = X::load(pa + f * 32 * kRB, off[0] + t * NTC);
             const typename X::Frag a1 = X::load(pa + f * 32 * kRB, off[1] + t * NTC);
 #pragma unroll
-            for (int e = 0; e < X::NSUB; ++e) {
-                X::mfma(re[f], a0, b0, e);             // + xr_i xr_j
-                X::mfma(im[f], a0, b1, e);             // + xr_i xi_j
-                X::mfma(re[f], a1, b1, e);             // + xi_i xi_j
-                X::mfma(im[f], a1, nb, e);             // - xi_i xr_j
+            for (int c = 0; c < FC; ++c) {
+#pragma unroll
+                for (int e = 0; e < X::NSUB; ++e) {
+                    X::mfma(re[f][c], a0, b0[c], e);   // + xr_i xr_j
+                    X::mfma(im[f][c], a0, b1[c], e);   // + xr_i xi_j
+                    X::mfma(re[f][c], a1, b1[c], e);   // + xi_i xi_j
+                    X::mfma(im[f][c], a1, nb[c], e);   // - xi_i xr_j
+                }
             }
         }
     }
 }
 
-// Asynchronous copy of 16 bytes per lane from global memory into LDS at
-// lds + 16 * lane (the LDS address is taken from M0).  Issued as inline
+// ---- FP32 on the BF16 matrix cores ------------------------------------------
+// A float32 is the exact sum of three BF16 values (8 significand bits each,
+// rounded to nearest, so the parts carry signs and all 24 bits are held).  Of
+// the nine products of two such sums the six largest are formed; what is left
+// out is below 2^-25 of the product, with either sign.  Six 32x32x16 BF16 MFMAs
+// (8 passes each) stand in for eight 32x32x2 FP32 ones (16 passes each).
+// Bound: the matrix cores' BF16 rate under the power limit (1024 inputs x 512
+// channels x 1024 spectra: 16.6 ms = 132 TFLOP/s with FP32 MFMAs, 11.6 ms = 190
+// TFLOP/s split, which is 1140 TFLOP/s of BF16 products; the BF16 library
+// product reaches 1158 on this card).  Error against 64 bits, relative to the
+// triangle's norm, same shape: 6.2e-7 with FP32 MFMAs, 1.5e-7 split (16 spectra:
+// 9.8e-8 and 6.8e-8).
+//
+// The matrix cores take BF16 values and products below the normal range as
+// zero, an error of 2^-126 in each of A * 24 products.  That is nothing beside
+// sqrt(C_ii C_jj) where both inputs have a value of at least kLeast (2^-40) in the
+// integration, or are zero.
+constexpr float kLeast = 0x1p-40f;
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+struct Split {
+    i32x4 p[3];                                        // 8 spectra of each part, largest first
+};
+
+typedef float f32x8 __attribute__((ext_vector_type(8)));
+
+// The lane's 8 spectra of one (row, plane) and stage.
+__device__ __forceinline__ f32x8 load8(const uint8_t *p, int o) {
+    const f32x4 a = *reinterpret_cast<const f32x4 *>(p + o), b = *reinterpret_cast<const f32x4 *>(p + (o ^ 16));
+    return f32x8{a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
+}
+
+// The same, split; most: their largest magnitude so far.
+__device__ __forceinline__ Split split8(f32x8 v, float &most) {
+    Split s;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        float x = v[2 * i], y = v[2 * i + 1];
+        most = __builtin_fmaxf(__builtin_fmaxf(most, __builtin_fabsf(x)), __builtin_fabsf(y));
+#pragma unroll
+        for (int q = 0; q < 3; ++q) {
+            const bf16x2 h{(__bf16)x, (__bf16)y};
+            const uint32_t u = __builtin_bit_cast(uint32_t, h);
+            s.p[q][i] = (int)u;
+            if (q < 2) {
+                x -= __builtin_bit_cast(float, u << 16);
+                y -= __builtin_bit_cast(float, u & 0xffff0000u);
+            }
+        }
+    }
+    return s;
+}
+
+__device__ __forceinline__ void mfma_bf16(f32x16 &c, i32x4 a, i32x4 b) {
+    c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0,
+                                                0, 0);
+}
+
+// wave_stage for FP32, split.  a / b: where in LDS the lane's first chunk of the
+// real plane of its row (row block 0) and column (column block 0) is; the
+// other chunks and the imaginary plane differ from it by one bit each.  The
+// real sums take a stage's 16 spectra from zero, smallest products first, and
+// are added to the running ones on the vector ALU: with the products going
+// straight into the running sums the autos, which only grow, lost accuracy
+// (1024 spectra: 1.3e-6 against 6.2e-7 with FP32 MFMAs); the imaginary sums,
+// which have no such terms, did not, and go straight in.  a1 is negated in
+// place for the products that enter with a minus sign.
+template <int FR, int FC, typename Acc>
+__device__ __forceinline__ void wave_stage_split(Acc (&re)[FR][FC], Acc (&im)[FR][FC], const uint8_t *smem, int a,
+                                                 int b, float (&most)[FR + FC]) {
+    // (a wave of one block, with registers to spare, reads everything at once)
+    f32x8 ra0, ra1;
+    if constexpr (FR * FC == 1) {
+        ra0 = load8(smem, a);
+        ra1 = load8(smem, a ^ kRowBytes);
+    }
+    Split b0[FC], b1[FC];
+#pragma unroll
+    for (int c = 0; c < FC; ++c) {
+        const f32x8 r0 = load8(smem + c * 32 * kRB, b), r1 = load8(smem + c * 32 * kRB, b ^ kRowBytes);
+        b0[c] = split8(r0, most[c]);
+        b1[c] = split8(r1, most[c]);
+    }
+    constexpr int PA[6] = {0, 1, 2, 0, 1, 0}, PB[6] = {2, 1, 0, 1, 0, 0};
+#pragma unroll
+    for (int f = 0; f < FR; ++f) {
+        if constexpr (FR * FC > 1) {
+            ra0 = load8(smem + f * 32 * kRB, a);
+            ra1 = load8(smem + f * 32 * kRB, a ^ kRowBytes);
+        }
+        const Split a0 = split8(ra0, most[FC + f]);
+        Split a1 = split8(ra1, most[FC + f]);
+#pragma unroll
+        for (int c = 0; c < FC; ++c) {
+            Acc r = {0};
+#pragma unroll
+            for (int q = 0; q < 6; ++q) {
+                mfma_bf16(r, a1.p[PA[q]], b1[c].p[PB[q]]);             // + xi_i xi_j
+                mfma_bf16(im[f][c], a0.p[PA[q]], b1[c].p[PB[q]]);      // + xr_i xi_j
+            }
+#pragma unroll
+            for (int q = 0; q < 3; ++q) a1.p[q] ^= (int)0x80008000u;
+#pragma unroll
+            for (int q = 0; q < 6; ++q) {
+                mfma_bf16(im[f][c], a1.p[PA[q]], b0[c].p[PB[q]]);      // - xi_i xr_j
+                mfma_bf16(r, a0.p[PA[q]], b0[c].p[PB[q]]);             // + xr_i xr_j
+            }
+            if (c + 1 < FC)
+#pragma unroll
+                for (int q = 0; q < 3; ++q) a1.p[q] ^= (int)0x80008000u;
+            re[f][c] += r;
+        }
+    }
+}
+
+// Asynchronous copy of 16 bytes per lane from global memory, base + off (base
+// uniform), into LDS at lds + 16 * lane (the LDS address is taken from M0).  Issued as inline
 // assembly so that the compiler, which cannot tell ring slots apart, does not
 // wait for every copy in flight before each LDS read; completion is awaited
 // explicitly with wait_vm.  The kernels here give the compiler no other use
 // of M0.
 #pragma clang diagnostic push
 #pragma clang diagnostic ignored "-Winline-asm"
-__device__ __forceinline__ void dma16(gu8 *src, uint32_t lds) {
-    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(src), "s"(lds)
+__device__ __forceinline__ void dma16(gu8 *base, uint32_t off, uint32_t lds) {
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" : : "v"(off), "s"(base), "s"(lds)
                  : "memory", "m0");
 }
 
@@ -234,6 +367,10 @@ template <int n> __device__ __forceinline__ void wait_vm() {
     __builtin_amdgcn_s_waitcnt((n & 15) | (7 << 4) | (15 << 8) | ((n >> 4) << 14));
 }
 
+// A value that is the same in every lane, kept in a scalar register (integer
+// divisions run on the vector ALU and would leave it in a vector one).
+__device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
+
 // Where a block's results go.  Triangle (RECT = false): the lower-triangle
 // product i(i+1)/2 + j of rows and columns below N with j <= i, B per
 // channel.  Rectangle (RECT = true): rows [r0, r_end) x columns [c0, c_end),
@@ -244,7 +381,7 @@ struct OutMap {
 };
 
 // The whole K loop and epilogue of one TILE x TILE block of channel k, rows
-// I0.., columns J0.., by the waves of WaveGrid<TILE>.
+// I0.., columns J0.., by the waves of WaveGrid<PREC, TILE>.
 // Time blocks stream through a two-slot LDS ring by direct global-to-LDS
 // copies: the copy of time block t + 1 is issued when block t starts and
 // lands while its MFMAs run.  The copies bypass registers, so the block
@@ -263,8 +400,8 @@ __device__ __forceinline__ void tile(uint8_t *smem, const uint8_t *__restrict__ 
     using Acc = typename XT<PREC, NT>::Acc;
     constexpr int ES = PREC == P_FP32 ? 4 : (PREC == P_FP16 ? 2 : 1);
     constexpr int TB = kRowBytes / ES;
-    using G = WaveGrid<TILE>;
-    constexpr int QS = G::QS, FR = G::FR, WC = G::WC, NW = G::NW, THREADS = G::THREADS;
+    using G = WaveGrid<PREC, TILE>;
+    constexpr int QS = G::QS, QC = G::QC, FR = G::FR, FC = G::FC, WC = G::WC, NW = G::NW, THREADS = G::THREADS;
     constexpr int OPB = TILE * RB;                      // one operand slab of a stage
     constexpr int STG = 2 * OPB;                        // one stage
     constexpr int L = STG / (NW * 1024);                // 1 KB copies per wave per stage
@@ -278,35 +415,40 @@ __device__ __forceinline__ void tile(uint8_t *smem, const uint8_t *__restrict__ 
     // rows or columns all lie past the inputs (past the rectangle) idles; one
     // whose last 32 rows do skips that row block.
     const int rlim = RECT ? om.r_end : N, clim = RECT ? om.c_end : N;
-    const bool dwave = FR > 1 && diag && 32 * wj > wi * QS + 31;
-    const bool lwave = FR > 1 && I0 + wi * QS + (FR - 1) * 32 >= rlim;
-    const bool active = !(diag && 32 * wj > wi * QS + QS - 1) && I0 + wi * QS < rlim && J0 + wj * 32 < clim &&
+    const bool dwave = FR > 1 && FC == 1 && diag && 32 * wj > wi * QS + 31;
+    const bool lwave = FR > 1 && FC == 1 && I0 + wi * QS + (FR - 1) * 32 >= rlim;
+    const bool active = !(diag && QC * wj > wi * QS + QS - 1) && I0 + wi * QS < rlim && J0 + wj * QC < clim &&
                         !(dwave && lwave);
     const int S = n_tb;                                 // stages
 
     // Copy j of this wave covers stage bytes [g KB, (g + 1) KB), g = NW j + wave;
     // lane l writes bytes 16 l of it: slab o, row r, slot sl, which holds
     // chunk c = sl ^ swz(r), i.e. bytes [16 (c % CPP), +16) of plane c / CPP.
-    int rowoff[L];
-#pragma unroll
-    for (int j = 0; j < L; ++j) {
-        const int bo = (NW * j + wave) * 1024 + 16 * lane;
-        const int o = bo / OPB, r = (bo % OPB) / RB, c = ((bo % RB) / 16) ^ swz(r);
-        const int pr = min((o ? J0 : I0) + r, N - 1);
-        rowoff[j] = pr * RB + (c / CPP) * kRowBytes + (c % CPP) * 16;
-    }
+    // The swizzled chunk is the same for every j: NW copies advance a multiple
+    // of 16 rows.
+    static_assert(NW * 1024 / RB % 16 == 0 && OPB % (NW * 1024) == 0, "copies advance whole swizzle periods");
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t *)smem;
-    gu8 *const gbase = (gu8 *)base_k;
+    const uint64_t gaddr = (uint64_t)(uintptr_t)base_k;
+    gu8 *const gbase = (gu8 *)(uintptr_t)((uint64_t)(uint32_t)uniform((int)(uint32_t)gaddr) |
+                                          (uint64_t)(uint32_t)uniform((int)(gaddr >> 32)) << 32);
     // A diagonal block's two slabs are the same rows: it copies slab 0 only
     // (copies j < L / 2 cover stage bytes [0, OPB)) and reads both operands
     // from it.
     auto issue = [&](int t) {
         gu8 *src = gbase + (int64_t)t * t_stride;
-        const uint32_t dst = lds0 + (uint32_t)((t & 1) * STG);
+        const uint32_t dst = lds0 + (uint32_t)((t & 1) * STG + wave * 1024);
+        int x = tid;
+        if constexpr (PREC == P_FP32) asm volatile("" : "+v"(x));   // (rebuild the offsets: its registers are full)
+        const int r = x >> 3, c = (x & 7) ^ swz(r);
+        const uint32_t col = (uint32_t)((c / CPP) * kRowBytes + (c % CPP) * 16);
 #pragma unroll
-        for (int j = 0; j < L; ++j)
-            if (!diag || j < L / 2)
-                dma16(src + rowoff[j], __builtin_amdgcn_readfirstlane(dst + (uint32_t)((NW * j + wave) * 1024)));
+        for (int j = 0; j < L; ++j) {
+            if (diag && j >= L / 2) continue;
+            constexpr int STEP = NW * 1024 / RB;       // rows per copy of the workgroup
+            const int row = min((j < L / 2 ? I0 + j * STEP : J0 + (j - L / 2) * STEP) + r, N - 1);
+            dma16(src, (uint32_t)row * RB + col,
+                  __builtin_amdgcn_readfirstlane(dst + (uint32_t)(NW * j * 1024)));
+        }
     };
     // Zero spectra >= tv of the landed last time block.
     auto fix_tail = [&](int t) {
@@ -335,49 +477,89 @@ __device__ __forceinline__ void tile(uint8_t *smem, const uint8_t *__restrict__ 
 #pragma unroll
         for (int t = 0; t < NT; ++t) off[pl][t] = 16 * ((pl * CPP + h * NT + t) ^ swz(m));
 
-    Acc re[FR], im[FR];
-#pragma unroll
-    for (int f = 0; f < FR; ++f)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            re[f][r] = 0;
-            im[f][r] = 0;
-        }
+    Acc re[FR][FC], im[FR][FC];
+    float most[FR + FC] = {};                          // (FP32) the lane's columns' and rows' largest values
 
     const uint8_t *pa0 = smem + (wi * QS + m) * RB;
-    const uint8_t *pb0 = smem + (diag ? 0 : OPB) + (wj * 32 + m) * RB;
+    const uint8_t *pb0 = smem + (diag ? 0 : OPB) + (wj * QC + m) * RB;
     const bool tail = tv < TB;
 
-    __builtin_amdgcn_s_setprio(2);                     // (see the copies in the loop)
-    issue(0);
-    __builtin_amdgcn_s_setprio(0);
-    for (int t = 0; t < S; ++t) {
-        wait_vm<0>();                                   // this wave's copies of block t landed
-        __syncthreads();                                // block t landed; the other slot is free
-        // The copies go out at a raised wave priority, ahead of the MFMAs of
-        // the other waves on the SIMD (FP32, 1024 x 4096 x 1024: 137.0 ->
-        // 133.3 ms; the FP16, FP8 and int8 forms unchanged within 1%; the
-        // first block's copies too: a further 0.2-1%).
-        __builtin_amdgcn_s_setprio(2);
-        if (t + 1 < S) issue(t + 1);
+    // The sums over all stages; SPLIT (FP32): on the BF16 matrix cores.
+    auto sum = [&](auto split) {
+        constexpr bool SPLIT = decltype(split)::value;
+#pragma unroll
+        for (int f = 0; f < FR; ++f)
+#pragma unroll
+            for (int c = 0; c < FC; ++c)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    re[f][c][r] = 0;
+                    im[f][c][r] = 0;
+                }
+        __builtin_amdgcn_s_setprio(2);                 // (see the copies in the loop)
+        issue(0);
         __builtin_amdgcn_s_setprio(0);
-        if (tail && t == S - 1) {
-            fix_tail(t);
-            __syncthreads();
-        }
-        if (active) {
+        for (int t = 0; t < S; ++t) {
+            wait_vm<0>();                               // this wave's copies of block t landed
+            __syncthreads();                            // block t landed; the other slot is free
+            // The copies go out at a raised wave priority, ahead of the MFMAs of
+            // the other waves on the SIMD (the first block's copies too: a
+            // further 0.2-1%; the FP16, FP8 and int8 forms otherwise
+            // unchanged within 1%).
+            __builtin_amdgcn_s_setprio(2);
+            if (t + 1 < S) issue(t + 1);
+            __builtin_amdgcn_s_setprio(0);
+            if (tail && t == S - 1) {
+                fix_tail(t);
+                __syncthreads();
+            }
+            if (!active) continue;
             const int so = (t & 1) * STG;
             // one uniform branch per stage keeps the MFMA stream branch-free
-            if (dwave)
-                wave_stage<PREC, FR, 1>(re, im, pa0 + so, pb0 + so, off);
-            else if (PREC != P_FP8 && lwave)           // (a third FP8 body would spill)
-                wave_stage<PREC, FR, 2>(re, im, pa0 + so, pb0 + so, off);
-            else
-                wave_stage<PREC, FR, 0>(re, im, pa0 + so, pb0 + so, off);
+            if constexpr (SPLIT) {
+                int x = tid;
+                asm volatile("" : "+v"(x));            // (rebuilt, not kept: see issue)
+                const int row = x & 31, w = x >> 6, chunk = 16 * ((x >> 5 & 1) * NT ^ swz(row));
+                wave_stage_split<FR, FC, Acc>(re, im, smem + so, (w / WC * QS + row) * RB + chunk,
+                                              (diag ? 0 : OPB) + (w % WC * QC + row) * RB + chunk, most);
+            } else if constexpr (PREC == P_FP32) {
+                wave_stage<PREC, FR, FC, 0>(re, im, pa0 + so, pb0 + so, off);
+            } else {
+                if (dwave) wave_stage<PREC, FR, FC, 1>(re, im, pa0 + so, pb0 + so, off);
+                else if (PREC != P_FP8 && lwave)       // (a third FP8 body would spill)
+                    wave_stage<PREC, FR, FC, 2>(re, im, pa0 + so, pb0 + so, off);
+                else wave_stage<PREC, FR, FC, 0>(re, im, pa0 + so, pb0 + so, off);
+            }
         }
+    };
+    if constexpr (PREC == P_FP32) {
+        // Under one whole block of spectra there are too few roundings for the
+        // split to gain accuracy (1 to 3 spectra: 5e-8 against 3e-8 to 5e-8
+        // relative), and little to do: FP32 MFMAs.  They also sum a block
+        // again where the split met values it cannot carry: an input's too small
+        // (see kLeast), or one that left a sum that is not finite.
+        bool plain = S == 1 && tail;
+        if (!plain) {
+            sum(std::true_type{});
+            float bad = 0.0f;
+            if (active) {
+#pragma unroll
+                for (int f = 0; f < FR; ++f)
+#pragma unroll
+                    for (int c = 0; c < FC; ++c)
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) bad += 0.0f * re[f][c][r] + 0.0f * im[f][c][r];
+            }
+            #pragma unroll
+            for (int i = 0; i < FR + FC; ++i)
+                if (most[i] != 0.0f && most[i] < kLeast) bad = 1.0f;
+            plain = __syncthreads_or(bad != 0.0f);
+        }
+        if (plain) sum(std::false_type{});
+    } else {
+        sum(std::false_type{});
     }
     if (!active) return;
-
     // Epilogue: element r of a 32x32 block is (row 8(r/4) + 4h + r%4, column m).
     // Rows go in batches of EH; each batch's accumulator reads are issued
     // before any of its writes.  The writes are streaming (non-temporal) so
@@ -391,13 +573,15 @@ __device__ __forceinline__ void tile(uint8_t *smem, const uint8_t *__restrict__ 
     gT2 *out = (gT2 *)acc_out + (int64_t)k * B;
     const gT2 *in = (const gT2 *)acc_in + (int64_t)k * B;   // the sums so far (== out except when dumping)
     const float s2 = (PREC != P_INT8 && scale2) ? ((gf32 *)scale2)[k] : 1.0f;
-    const int j = J0 + wj * 32 + m;
     // rows of a block per batch of accumulator reads: all 16 where a wave has
     // one row block, 8 where it has two (the registers allow no more)
     constexpr int EH = FR == 1 ? 16 : 8;
 #pragma unroll
-    for (int f = 0; f < FR; ++f) {
-        if ((dwave && f == 0) || (lwave && f == FR - 1)) continue;
+    for (int f = 0; f < FR; ++f)
+#pragma unroll
+    for (int c = 0; c < FC; ++c) {
+        if ((dwave && skipped<FR, 1>(f)) || (lwave && skipped<FR, 2>(f))) continue;
+        const int j = J0 + wj * QC + 32 * c + m;
 #pragma unroll
         for (int hh = 0; hh < 16 / EH; ++hh) {
             int idx[EH];
@@ -430,9 +614,9 @@ __device__ __forceinline__ void tile(uint8_t *smem, const uint8_t *__restrict__ 
                 T2 v;
                 const bool auto_ = !RECT && i == j;
                 if constexpr (PREC == P_INT8) {
-                    v = T2{re[f][r], auto_ ? 0 : im[f][r]};
+                    v = T2{re[f][c][r], auto_ ? 0 : im[f][c][r]};
                 } else {
-                    v = T2{re[f][r] * s2, auto_ ? 0.0f : im[f][r] * s2};
+                    v = T2{re[f][c][r] * s2, auto_ ? 0.0f : im[f][c][r] * s2};
                 }
                 if (!first_call) {
                     v.x += old[q].x;
@@ -458,7 +642,7 @@ __device__ __forceinline__ void tri_block(int t, int &bi, int &bj) {
 // call of an integration whatever first_call says (the accumulators of a
 // batch sub-array are then logically zero, whatever they hold).
 template <int PREC, int TILE>
-__global__ __launch_bounds__(WaveGrid<TILE>::THREADS) __attribute__((amdgpu_waves_per_eu(4))) void xengine_kernel(
+__global__ __launch_bounds__((WaveGrid<PREC, TILE>::THREADS)) __attribute__((amdgpu_waves_per_eu((WaveGrid<PREC, TILE>::EU)))) void xengine_kernel(
     const uint8_t *__restrict__ spec, int N, int n_tiles, int n_work, int n_tb, int tv,
     int64_t k_stride, int64_t t_stride, const float *__restrict__ scale2, void *__restrict__ acc_out,
     const void *acc_in, int64_t B, int first_call, const int *__restrict__ zflag) {
@@ -466,9 +650,11 @@ __global__ __launch_bounds__(WaveGrid<TILE>::THREADS) __attribute__((amdgpu_wave
     const int per = (n_work + 7) / 8;
     const int w = (blockIdx.x % 8) * per + blockIdx.x / 8;
     if (w >= n_work) return;
-    const int k = w / n_tiles;
+    const int k = uniform(w / n_tiles);
     int bi, bj;
     tri_block(w % n_tiles, bi, bj);
+    bi = uniform(bi);
+    bj = uniform(bj);
     const int fc = zflag && *zflag ? 1 : first_call;
     tile<PREC, TILE>(smem, spec + (int64_t)k * k_stride, t_stride, N, n_tb, tv, bi * TILE, bj * TILE, k, scale2,
                      acc_out, acc_in, B, fc, threadIdx.x);
@@ -477,7 +663,7 @@ __global__ __launch_bounds__(WaveGrid<TILE>::THREADS) __attribute__((amdgpu_wave
 // Rectangle X-engine: rows [r0, r0 + ni) against columns [c0, c0 + nj) in
 // TILE x TILE blocks (nbi x nbj per channel), XCD-major like xengine_kernel.
 template <int PREC, int TILE>
-__global__ __launch_bounds__(WaveGrid<TILE>::THREADS) __attribute__((amdgpu_waves_per_eu(4))) void xengine_rect_kernel(
+__global__ __launch_bounds__((WaveGrid<PREC, TILE>::THREADS)) __attribute__((amdgpu_waves_per_eu((WaveGrid<PREC, TILE>::EU)))) void xengine_rect_kernel(
     const uint8_t *__restrict__ spec, int N, int nbi, int nbj, int n_work, int n_tb, int tv, int64_t k_stride,
     int64_t t_stride, const float *__restrict__ scale2, void *__restrict__ out, int64_t B, int first_call, OutMap om) {
     __shared__ __attribute__((aligned(16))) uint8_t smem[ring_bytes(TILE)];
@@ -485,7 +671,7 @@ __global__ __launch_bounds__(WaveGrid<TILE>::THREADS) __attribute__((amdgpu_wave
     const int w = (blockIdx.x % 8) * per + blockIdx.x / 8;
     if (w >= n_work) return;
     const int nb = nbi * nbj;
-    const int k = w / nb, bi = (w % nb) / nbj, bj = w % nbj;
+    const int k = uniform(w / nb), bi = uniform((w % nb) / nbj), bj = uniform(w % nbj);
     tile<PREC, TILE, true>(smem, spec + (int64_t)k * k_stride, t_stride, N, n_tb, tv, om.r0 + bi * TILE,
                            om.c0 + bj * TILE, k,
                            scale2, out, out, B, first_call, threadIdx.x, om);
@@ -502,7 +688,7 @@ __global__ __launch_bounds__(WaveGrid<TILE>::THREADS) __attribute__((amdgpu_wave
 // descriptors follow their sorted order (largest item first) and a workgroup
 // finds its descriptor by binary search over the queue offsets.
 template <int PREC, int TILE>
-__global__ __launch_bounds__(WaveGrid<TILE>::THREADS) __attribute__((amdgpu_waves_per_eu(4))) void xengine_batched_kernel(
+__global__ __launch_bounds__((WaveGrid<PREC, TILE>::THREADS)) __attribute__((amdgpu_waves_per_eu((WaveGrid<PREC, TILE>::EU)))) void xengine_batched_kernel(
     const XQueue *__restrict__ plan, const XDesc *__restrict__ all_desc, unsigned int *__restrict__ counter) {
     __shared__ __attribute__((aligned(16))) uint8_t smem[ring_bytes(TILE)];
     __shared__ unsigned int s_item;
@@ -587,7 +773,7 @@ hipError_t launch_x(int C, int N, int n_spectra, const void *spec, SpecLayout la
     if (n_tb <= 0 || n_work <= 0 || n_work > ((int64_t)1 << 30)) return hipErrorInvalidValue;
     const int grid = (int)((n_work + 7) / 8) * 8;
     const int64_t B = (int64_t)N * (N + 1) / 2;
-    hipLaunchKernelGGL((xengine_kernel<PREC, TILE>), dim3(grid), dim3(WaveGrid<TILE>::THREADS), 0, stream,
+    hipLaunchKernelGGL((xengine_kernel<PREC, TILE>), dim3(grid), dim3(WaveGrid<PREC, TILE>::THREADS), 0, stream,
                        static_cast<const uint8_t *>(spec), N, n_tiles, (int)n_work, n_tb, tv, lay.ks, lay.ts,
                        scale2, acc, acc_in, B, first_call, zflag);
     return hipGetLastError();
@@ -608,7 +794,8 @@ hipError_t launch_xp(int tile, int C, int N, int n_spectra, const void *spec, Sp
 
 template <int PREC, int TILE>
 hipError_t launch_rect_t(int C, int N, int n_spectra, const void *spec, SpecLayout lay, const float *scale2,
-                         void *out, int first_call, int r0, int ni, int c0, int nj, hipStream_t stream) {
+                         void *out, int first_call, int r0, int ni, int c0, int nj,
+                         hipStream_t stream) {
     const int TB = time_block(PREC);
     const int n_tb = (n_spectra + TB - 1) / TB;
     const int tv = n_spectra - (n_tb - 1) * TB;
@@ -617,7 +804,7 @@ hipError_t launch_rect_t(int C, int N, int n_spectra, const void *spec, SpecLayo
     if (n_tb <= 0 || n_work <= 0 || n_work > ((int64_t)1 << 30) || r0 < 0 || c0 < 0 || r0 + ni > N || c0 + nj > N)
         return hipErrorInvalidValue;
     const int grid = (int)((n_work + 7) / 8) * 8;
-    hipLaunchKernelGGL((xengine_rect_kernel<PREC, TILE>), dim3(grid), dim3(WaveGrid<TILE>::THREADS), 0, stream,
+    hipLaunchKernelGGL((xengine_rect_kernel<PREC, TILE>), dim3(grid), dim3(WaveGrid<PREC, TILE>::THREADS), 0, stream,
                        static_cast<const uint8_t *>(spec), N, nbi, nbj, (int)n_work, n_tb, tv,
                        lay.ks, lay.ts, scale2, out, (int64_t)ni * nj, first_call,
                        OutMap{r0, r0 + ni, c0, c0 + nj});
@@ -664,7 +851,7 @@ hipError_t launch_xengine(int prec, int tile, int C, int N, int n_spectra, const
 template <int PREC, int TILE>
 hipError_t launch_batched_t(const XQueue *d_plan, const XDesc *d_desc, unsigned int *counter, int grid,
                             hipStream_t stream) {
-    hipLaunchKernelGGL((xengine_batched_kernel<PREC, TILE>), dim3(grid), dim3(WaveGrid<TILE>::THREADS), 0, stream, d_plan, d_desc,
+    hipLaunchKernelGGL((xengine_batched_kernel<PREC, TILE>), dim3(grid), dim3(WaveGrid<PREC, TILE>::THREADS), 0, stream, d_plan, d_desc,
                        counter);
     return hipGetLastError();
 }
