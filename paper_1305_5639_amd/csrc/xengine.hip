@@ -190,7 +190,9 @@ template <int FR, int SKIP> constexpr bool skipped(int f) {
 // are read once, each row block's fragments just before its MFMAs, and
 // (except for FP8, whose MFMA takes both chunks) one 16-byte chunk at a time,
 // which keeps the live fragment registers few enough for four waves per SIMD.
-template <int PREC, int FR, int FC, int SKIP, typename Acc>
+// TRI: rows and columns are the same, and blocks above the diagonal are left
+// out.
+template <int PREC, int FR, int FC, int SKIP, bool TRI = false, typename Acc>
 __device__ __forceinline__ void wave_stage(Acc (&re)[FR][FC], Acc (&im)[FR][FC], const uint8_t *pa,
                                            const uint8_t *pb, const int (&off)[2][kNT]) {
     constexpr int NC = PREC == P_FP8 ? 1 : kNT;        // chunk groups per stage
@@ -215,10 +217,11 @@ __device__ __forceinline__ void wave_stage(Acc (&re)[FR][FC], Acc (&im)[FR][FC],
 #pragma unroll
         for (int f = 0; f < FR; ++f) {
             if (skipped<FR, SKIP>(f)) continue;
-            const typename X::Frag a0 = X::load(pa + f * 32 * kRB, off[0] + t * NTC);
-            const typename X::Frag a1 = X::load(pa + f * 32 * kRB, off[1] + t * NTC);
+            const typename X::Frag a0 = TRI ? b0[f] : X::load(pa + f * 32 * kRB, off[0] + t * NTC);
+            const typename X::Frag a1 = TRI ? b1[f] : X::load(pa + f * 32 * kRB, off[1] + t * NTC);
 #pragma unroll
             for (int c = 0; c < FC; ++c) {
+                if (TRI && c > f) continue;
 #pragma unroll
                 for (int e = 0; e < X::NSUB; ++e) {
                     X::mfma(re[f][c], a0, b0[c], e);   // + xr_i xr_j
@@ -298,12 +301,12 @@ __device__ __forceinline__ void mfma_bf16(f32x16 &c, i32x4 a, i32x4 b) {
 // (1024 spectra: 1.3e-6 against 6.2e-7 with FP32 MFMAs); the imaginary sums,
 // which have no such terms, did not, and go straight in.  a1 is negated in
 // place for the products that enter with a minus sign.
-template <int FR, int FC, typename Acc>
+template <int FR, int FC, bool TRI = false, typename Acc>
 __device__ __forceinline__ void wave_stage_split(Acc (&re)[FR][FC], Acc (&im)[FR][FC], const uint8_t *smem, int a,
                                                  int b, float (&most)[FR + FC]) {
     // (a wave of one block, with registers to spare, reads everything at once)
     f32x8 ra0, ra1;
-    if constexpr (FR * FC == 1) {
+    if constexpr (FR * FC == 1 && !TRI) {
         ra0 = load8(smem, a);
         ra1 = load8(smem, a ^ kRowBytes);
     }
@@ -317,14 +320,15 @@ __device__ __forceinline__ void wave_stage_split(Acc (&re)[FR][FC], Acc (&im)[FR
     constexpr int PA[6] = {0, 1, 2, 0, 1, 0}, PB[6] = {2, 1, 0, 1, 0, 0};
 #pragma unroll
     for (int f = 0; f < FR; ++f) {
-        if constexpr (FR * FC > 1) {
+        if constexpr (FR * FC > 1 && !TRI) {
             ra0 = load8(smem + f * 32 * kRB, a);
             ra1 = load8(smem + f * 32 * kRB, a ^ kRowBytes);
         }
-        const Split a0 = split8(ra0, most[FC + f]);
-        Split a1 = split8(ra1, most[FC + f]);
+        const Split a0 = TRI ? b0[f] : split8(ra0, most[FC + f]);
+        Split a1 = TRI ? b1[f] : split8(ra1, most[FC + f]);
 #pragma unroll
         for (int c = 0; c < FC; ++c) {
+            if (TRI && c > f) continue;
             Acc r = {0};
 #pragma unroll
             for (int q = 0; q < 6; ++q) {
@@ -338,7 +342,7 @@ __device__ __forceinline__ void wave_stage_split(Acc (&re)[FR][FC], Acc (&im)[FR
                 mfma_bf16(im[f][c], a1.p[PA[q]], b0[c].p[PB[q]]);      // - xi_i xr_j
                 mfma_bf16(r, a0.p[PA[q]], b0[c].p[PB[q]]);             // + xr_i xr_j
             }
-            if (c + 1 < FC)
+            if (c + 1 < FC && !(TRI && c == f))
 #pragma unroll
                 for (int q = 0; q < 3; ++q) a1.p[q] ^= (int)0x80008000u;
             re[f][c] += r;
@@ -520,7 +524,7 @@ __device__ __forceinline__ void tile(uint8_t *smem, const uint8_t *__restrict__ 
                 int x = tid;
                 asm volatile("" : "+v"(x));            // (rebuilt, not kept: see issue)
                 const int row = x & 31, w = x >> 6, chunk = 16 * ((x >> 5 & 1) * NT ^ swz(row));
-                wave_stage_split<FR, FC, Acc>(re, im, smem + so, (w / WC * QS + row) * RB + chunk,
+                wave_stage_split<FR, FC>(re, im, smem + so, (w / WC * QS + row) * RB + chunk,
                                               (diag ? 0 : OPB) + (w % WC * QC + row) * RB + chunk, most);
             } else if constexpr (PREC == P_FP32) {
                 wave_stage<PREC, FR, FC, 0>(re, im, pa0 + so, pb0 + so, off);
@@ -660,6 +664,178 @@ __global__ __launch_bounds__((WaveGrid<PREC, TILE>::THREADS)) __attribute__((amd
                      acc_out, acc_in, B, fc, threadIdx.x);
 }
 
+// Small arrays, N <= 32 NB inputs (NB = 1, or 2 for FP32): one workgroup per channel,
+// whose waves each take every KS-th time block of the whole triangle into
+// accumulators of their own, through a two-slot ring of their own, and add them
+// up through LDS at the end.  What bounds such an array is the chain of time
+// blocks, each a copy's latency and a few MFMAs long: in a 64-input block one to
+// three waves out of four walked all of it behind a barrier per time block.
+// Bounds: copy latency (16 inputs x 64 channels x 1024 FP32 spectra: 74 -> 14 us)
+// and, with many channels, the matrix cores' idle half and the copies (16 x 8192
+// x 1024 int8: 95 -> 62 us, 4.3 TB/s).
+template <int NB> struct SmallGrid {
+    static constexpr int KS = NB == 1 ? 8 : 4;         // waves
+    static constexpr int THREADS = 64 * KS;
+    static constexpr int STG = NB * 32 * kRB;          // bytes of a stage
+    static constexpr int L = STG / 1024;               // 1 KB copies per stage
+    static constexpr int EU = NB == 1 ? 4 : 2;         // waves per SIMD (two workgroups per CU by LDS)
+};
+
+template <int PREC, int NB>
+__global__ __launch_bounds__((SmallGrid<NB>::THREADS)) __attribute__((amdgpu_waves_per_eu((SmallGrid<NB>::EU)))) void xengine_small_kernel(
+    const uint8_t *__restrict__ spec, int N, int C, int n_tb, int tv, int64_t k_stride, int64_t t_stride,
+    const float *__restrict__ scale2, void *__restrict__ acc_out, const void *acc_in, int64_t B, int first_call,
+    const int *__restrict__ zflag) {
+    using G = SmallGrid<NB>;
+    using Acc = typename XT<PREC, kNT>::Acc;
+    using E = typename std::conditional<PREC == P_INT8, int, float>::type;
+    constexpr int KS = G::KS, STG = G::STG, L = G::L;
+    constexpr int ES = PREC == P_FP32 ? 4 : (PREC == P_FP16 ? 2 : 1);
+    __shared__ __attribute__((aligned(16))) uint8_t smem[KS * 2 * STG];
+    const int per = (C + 7) / 8;
+    const int k = (blockIdx.x % 8) * per + blockIdx.x / 8;   // XCD-major
+    if (k >= C) return;
+    const int wave = uniform(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int m = lane & 31, h = lane >> 5;
+    const int n = n_tb > wave ? (n_tb - wave + KS - 1) / KS : 0;   // this wave's time blocks
+    uint8_t *const ring = smem + wave * 2 * STG;
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t *)ring;
+    gu8 *const gbase = (gu8 *)spec + (int64_t)k * k_stride;
+
+    auto issue = [&](int i) {
+        gu8 *src = gbase + (int64_t)(wave + KS * i) * t_stride;
+#pragma unroll
+        for (int j = 0; j < L; ++j) {
+            const int r = j * 8 + (lane >> 3), c = (lane & 7) ^ swz(r);
+            dma16(src, (uint32_t)(min(r, N - 1) * kRB + c * 16), uniform((int)(lds0 + (i & 1) * STG + j * 1024)));
+        }
+    };
+    // Zero spectra >= tv of this wave's landed last time block.
+    auto fix_tail = [&](int i) {
+        for (int q = lane; q < STG / 16; q += 64) {
+            const int r = q / (kRB / 16), c = (q % (kRB / 16)) ^ swz(r);
+            const int first = (c % kCPP) * 16 / ES;
+            uint32_t *wd = reinterpret_cast<uint32_t *>(ring + (i & 1) * STG + q * 16);
+#pragma unroll
+            for (int d = 0; d < 4; ++d) {
+                uint32_t msk = 0;
+#pragma unroll
+                for (int bb = 0; bb < 4; ++bb)
+                    if (first + (4 * d + bb) / ES < tv) msk |= 0xffu << (8 * bb);
+                wd[d] &= msk;
+            }
+        }
+    };
+    int off[2][kNT];
+#pragma unroll
+    for (int pl = 0; pl < 2; ++pl)
+#pragma unroll
+        for (int t = 0; t < kNT; ++t) off[pl][t] = 16 * ((pl * kCPP + h * kNT + t) ^ swz(m));
+
+    const bool tail = tv < kRowBytes / ES;
+    Acc re[NB][NB], im[NB][NB];
+    float most[2 * NB] = {};
+    auto sum = [&](auto split) {
+#pragma unroll
+        for (int f = 0; f < NB; ++f)
+#pragma unroll
+            for (int c = 0; c <= f; ++c)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    re[f][c][r] = 0;
+                    im[f][c][r] = 0;
+                }
+        if (n > 0) issue(0);
+        for (int i = 0; i < n; ++i) {
+            // the slot's last reads are done; the next block goes out before
+            // this one is waited for
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            if (i + 1 < n) {
+                issue(i + 1);
+                asm volatile("s_waitcnt vmcnt(%0)" : : "n"(L) : "memory");
+            } else {
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            }
+            if (tail && wave + KS * i == n_tb - 1) {
+                fix_tail(i);
+                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            }
+            const uint8_t *p = ring + (i & 1) * STG + m * kRB;
+            if constexpr (decltype(split)::value)
+                wave_stage_split<NB, NB, true>(re, im, p, off[0][0], off[0][0], most);
+            else
+                wave_stage<PREC, NB, NB, 0, true>(re, im, p, p, off);
+        }
+    };
+    if constexpr (PREC == P_FP32) {                    // (the rules of tile())
+        bool plain = n_tb == 1 && tail;
+        if (!plain) {
+            sum(std::true_type{});
+            float bad = 0.0f;
+#pragma unroll
+            for (int f = 0; f < NB; ++f)
+#pragma unroll
+                for (int c = 0; c <= f; ++c)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) bad += 0.0f * re[f][c][r] + 0.0f * im[f][c][r];
+#pragma unroll
+            for (int i = 0; i < NB; ++i)
+                if (most[i] != 0.0f && most[i] < kLeast) bad = 1.0f;
+            plain = __syncthreads_or(bad != 0.0f);
+        }
+        if (plain) sum(std::false_type{});
+    } else {
+        sum(std::false_type{});
+    }
+
+    // Each block's sums of all waves through LDS; wave w then adds up and
+    // writes elements R w .. R w + R - 1 of it (their places as in tile()).
+    constexpr int R = 16 / KS;
+    static_assert(KS * 32 * 64 * 4 <= KS * 2 * STG, "the sums of a block fit the rings");
+    E *const red = reinterpret_cast<E *>(smem);
+    typedef E T2 __attribute__((ext_vector_type(2)));
+    typedef __attribute__((address_space(1))) T2 gT2;
+    gT2 *out = (gT2 *)acc_out + (int64_t)k * B;
+    const gT2 *in = (const gT2 *)acc_in + (int64_t)k * B;
+    const float s2 = (PREC != P_INT8 && scale2) ? ((gf32 *)scale2)[k] : 1.0f;
+    const bool write = (zflag && *zflag) || first_call;
+#pragma unroll
+    for (int f = 0; f < NB; ++f)
+#pragma unroll
+    for (int c = 0; c <= f; ++c) {
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            red[(wave * 32 + r) * 64 + lane] = re[f][c][r];
+            red[(wave * 32 + 16 + r) * 64 + lane] = im[f][c][r];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < R; ++q) {
+            const int r = R * wave + q;
+            const int i = 32 * f + 8 * (r >> 2) + 4 * h + (r & 3), j = 32 * c + m;
+            E a = red[r * 64 + lane], b = red[(16 + r) * 64 + lane];
+#pragma unroll
+            for (int w = 1; w < KS; ++w) {
+                a += red[(w * 32 + r) * 64 + lane];
+                b += red[(w * 32 + 16 + r) * 64 + lane];
+            }
+            if (i < N && j <= i) {
+                const int o = i * (i + 1) / 2 + j;
+                T2 v;
+                if constexpr (PREC == P_INT8) v = T2{a, i == j ? 0 : b};
+                else v = T2{a * s2, i == j ? 0.0f : b * s2};
+                if (!write) {
+                    const T2 old = in[o];
+                    v.x += old.x;
+                    v.y += old.y;
+                }
+                __builtin_nontemporal_store(v, &out[o]);
+            }
+        }
+    }
+}
+
 // Rectangle X-engine: rows [r0, r0 + ni) against columns [c0, c0 + nj) in
 // TILE x TILE blocks (nbi x nbj per channel), XCD-major like xengine_kernel.
 template <int PREC, int TILE>
@@ -779,10 +955,36 @@ hipError_t launch_x(int C, int N, int n_spectra, const void *spec, SpecLayout la
     return hipGetLastError();
 }
 
+template <int PREC, int NB>
+hipError_t launch_small(int C, int N, int n_spectra, const void *spec, SpecLayout lay, const float *scale2, void *acc,
+                        const void *acc_in, int first_call, const int *zflag, hipStream_t stream) {
+    const int TB = time_block(PREC);
+    const int n_tb = (n_spectra + TB - 1) / TB;
+    const int tv = n_spectra - (n_tb - 1) * TB;
+    if (n_tb <= 0 || C <= 0 || N < 1 || N > 32 * NB) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((xengine_small_kernel<PREC, NB>), dim3((C + 7) / 8 * 8), dim3(SmallGrid<NB>::THREADS), 0, stream,
+                       static_cast<const uint8_t *>(spec), N, C, n_tb, tv, lay.ks, lay.ts, scale2, acc, acc_in,
+                       (int64_t)N * (N + 1) / 2, first_call, zflag);
+    return hipGetLastError();
+}
+
 template <int PREC>
 hipError_t launch_xp(int tile, int C, int N, int n_spectra, const void *spec, SpecLayout lay,
                      const float *scale2, void *acc, const void *acc_in, int first_call, const int *zflag,
                      hipStream_t stream) {
+    // The small kernel from as many time blocks as its split of them gains from
+    // (its reduction costs the same whatever their number): FP32, whose blocks
+    // take longest, 32 inputs x 8192 channels: 2 blocks 59 -> 54 us, 4 blocks 92 ->
+    // 61, 16 blocks 270 -> 148; FP16 6 blocks 54 -> 47, 8 blocks 73 -> 58, int8 8
+    // blocks 76 -> 61, but int8 2 blocks 33 -> 38.  Over 32 inputs FP32 alone: 64 x
+    // 4096 channels, 4 blocks 84 -> 64 us, 32 blocks 517 -> 325; FP16 64 x 2048, 32
+    // blocks, 104 -> 112.
+    const int n_tb = (n_spectra + time_block(PREC) - 1) / time_block(PREC);
+    if (tile == 64 && N <= 32 && n_tb >= (PREC == P_FP32 ? 4 : 6))
+        return launch_small<PREC, 1>(C, N, n_spectra, spec, lay, scale2, acc, acc_in, first_call, zflag, stream);
+    if constexpr (PREC == P_FP32)
+        if (tile == 64 && N <= 64 && n_tb >= 4)
+            return launch_small<PREC, 2>(C, N, n_spectra, spec, lay, scale2, acc, acc_in, first_call, zflag, stream);
     if (tile == 64)
         return launch_x<PREC, 64>(C, N, n_spectra, spec, lay, scale2, acc, acc_in, first_call, zflag, stream);
     if (tile == 128)
