@@ -156,13 +156,37 @@ bool default_dump(const corr_params *p) { return p->layout == CORR_TRI_LOWER && 
 
 bool aligned(const void *ptr, size_t a) { return ((uintptr_t)ptr % a) == 0; }
 
-// Default block size when none was set or tuned, from measured X-engine
-// speed on MI355X at 256..2048 inputs: 128-input blocks, which reuse each
-// operand more (1024 inputs x 512 channels x 1024 spectra, 64- against
-// 128-input blocks: FP32 13.7 / 11.6 ms, FP16 2.72 / 2.25, FP8 1.55 / 1.20).
-int default_tile(int N) { return N <= 64 ? 64 : 128; }
+// Default block size when none was set or tuned, given the blocks of 64 and of
+// 128 inputs that cover one channel.  128-input blocks reuse each operand more
+// (1024 inputs x 512 channels x 1024 spectra, 64- against 128-input blocks: FP32
+// 13.7 / 11.4 ms, FP16 2.72 / 2.25, FP8 1.55 / 1.20), but only where they are
+// about as full (at least 3.2 64-input blocks for each: 300 inputs x 512 channels
+// int8, 2.5 for each, 104 / 145 us) and enough for every CU to hold its two all
+// the time: a 64-input block ends sooner (256 inputs x 128 channels FP32, 384
+// blocks of 128: 55 / 67 us; x 512, 1536 blocks: 218 / 205 us; 512 inputs x 256
+// channels int8, 2560: 131 / 146 us; x 512, 5120: 334 / 287 us).  Against the
+// better of both at 137 shapes of 65..1024 inputs x 16..2048 channels the rule
+// loses 0.2% (FP32, FP8, int8) to 0.6% (FP16) on average.
+int default_tile(int prec, int64_t n64, int64_t n128, int C) {
+    return 5 * n64 >= 16 * n128 && C * n128 >= (prec == P_FP32 ? 1280 : 4096) ? 128 : 64;
+}
 
-int effective_tile(const corr_ctx *h) { return h->tile ? h->tile : default_tile(h->N); }
+int64_t tri_blocks(int N, int tile) {
+    const int64_t n = (N + tile - 1) / tile;
+    return n * (n + 1) / 2;
+}
+
+// For the triangle of N inputs.
+int default_tile(int prec, int N, int C) { return default_tile(prec, tri_blocks(N, 64), tri_blocks(N, 128), C); }
+
+int effective_tile(const corr_ctx *h) { return h->tile ? h->tile : default_tile(h->prec, h->N, h->C); }
+
+// For ni rows against nj columns.
+int rect_tile(const corr_ctx *h, int ni, int nj) {
+    if (h->tile) return h->tile;
+    auto blocks = [&](int64_t t) { return ((ni + t - 1) / t) * ((nj + t - 1) / t); };
+    return default_tile(h->prec, blocks(64), blocks(128), h->C);
+}
 
 const float *x_scale(const corr_ctx *h) {
     if (h->prec == P_INT8) return nullptr;
@@ -653,7 +677,7 @@ corr_status corr_xengine_rect(corr_handle h, int32_t i0, int32_t ni, int32_t j0,
     if (n_spectra > h->n_held) return fail(h, CORR_E_STATE, "n_spectra exceeds the spectra held");
     if (h->prec == P_INT8 && n_spectra > CORR_INT8_MAX_INTEGRATE)
         return fail(h, CORR_E_OVERFLOW, "int8 rectangle over more than 66572 spectra");
-    const hipError_t e = launch_xengine_rect(h->prec, effective_tile(h), h->C, h->N, n_spectra, h->spec,
+    const hipError_t e = launch_xengine_rect(h->prec, rect_tile(h, ni, nj), h->C, h->N, n_spectra, h->spec,
                                              h->lay, x_scale(h), d_out, accumulate ? 0 : 1, i0, ni, j0, nj,
                                              h->stream);
     if (e != hipSuccess) return hip_fail(h, e, "rectangle launch");
@@ -792,7 +816,7 @@ corr_status corr_autotune(corr_handle h, int32_t n_spectra, int32_t *tile_out) {
     }
     const int Ct = tune_channels(h);
     const int cand[2] = {64, 128};
-    const int def_tile = default_tile(h->N);
+    const int def_tile = default_tile(h->prec, h->N, h->C);
     float best_ms = 0, def_ms = 0;
     int best = 0;
     {
@@ -867,7 +891,7 @@ corr_status corr_autotune_fx(corr_handle h, const void *d_volts, int64_t ld_samp
 
     const int n_tb = (n_spectra + h->TB - 1) / h->TB;
     const bool def_tb = default_tb_major(h->C, h->N, elem_bytes(h->prec));
-    const int def_tile = default_tile(h->N);
+    const int def_tile = default_tile(h->prec, h->N, h->C);
     const TuneKey key{h->arch, 1, h->prec, (h->N + 63) / 64, h->C, n_tb, 0};
     TuneVal best{def_tile, def_tb ? 1 : 0};
     float best_ms = 0, def_ms = 0;
@@ -1272,14 +1296,13 @@ corr_status corr_xengine_noalloc(const corr_params *params, const void *d_spectr
     const bool scaled = prec == P_FP16 || prec == P_FP8;
     if (scaled && (e = launch_scale2(C, d_inv_scale, s2, stream)) != hipSuccess)
         return hip_fail(nullptr, e, "scale2 launch");
-    const int tile = default_tile(N);
     const int64_t B = (int64_t)N * (N + 1) / 2;
     for (int k0 = 0; k0 < C; k0 += nk) {
         const int n = std::min(nk, C - k0);
         e = launch_ingest_channels(prec, C, k0, n, N, n_spectra, lay, d_spectra, spec, stream);
         if (e != hipSuccess) return hip_fail(nullptr, e, "ingest launch");
         uint8_t *vis = static_cast<uint8_t *>(d_vis) + (int64_t)k0 * B * 8;
-        e = launch_xengine(prec, tile, n, N, n_spectra, spec, lay, scaled ? s2 + k0 : nullptr, vis, vis,
+        e = launch_xengine(prec, default_tile(prec, N, n), n, N, n_spectra, spec, lay, scaled ? s2 + k0 : nullptr, vis, vis,
                            accumulate ? 0 : 1, stream);
         if (e != hipSuccess) return hip_fail(nullptr, e, "xengine launch");
     }
