@@ -1,6 +1,5 @@
 // Data-movement kernels around the two engines: caller spectra in and out of
-// the time-blocked planar layout, dump layout/order conversion, the s_k^2
-// table and a zero fill.  None of these is on the F -> X hot path; the
+// the time-blocked planar layout, dump layout/order conversion and a zero fill.  None of these is on the F -> X hot path; the
 // spectra moves are LDS-tiled transposes, the rest coalesced element maps.
 #include "corr_internal.h"
 
@@ -46,7 +45,8 @@ __device__ __forceinline__ uint32_t sat_int8x4(uint32_t v) {
 template <typename T, bool INGEST, bool VEC, bool SAT8 = false>
 __global__ __launch_bounds__(kThreads) void relayout_kernel(const uint8_t *__restrict__ src,
                                                              uint8_t *__restrict__ dst, int C, int N,
-                                                             int n_spectra, int n_tb, int n_cc, SpecLayout lay) {
+                                                             int n_spectra, int n_tb, int n_cc, SpecLayout lay,
+                                                             UserScale us) {
     constexpr int ES = (int)sizeof(T), TB = kRowBytes / ES, VE = 16 / ES, W = kCols * ES;
     constexpr int PUB_VECS = TB * (W / 16);             // 1024 either side
     __shared__ __align__(16) uint8_t lds[TB * W];
@@ -62,6 +62,9 @@ __global__ __launch_bounds__(kThreads) void relayout_kernel(const uint8_t *__res
         return ((int64_t)(tb * TB + t) * C + k) * pub_row + (int64_t)col * ES;
     };
     if (INGEST) {
+        if (us.scale2)
+            for (int64_t c = g * kThreads + threadIdx.x; c < us.C; c += (int64_t)gridDim.x * kThreads)
+                us.scale2[c] = us.inv ? square_of_scale(us.inv[c]) : 1.0f;
         for (int i = threadIdx.x; i < PUB_VECS; i += kThreads) {
             const int t = i / (W / 16), c = i % (W / 16);
             const int a = tb * TB + t, col0 = c_base + c * VE;
@@ -178,18 +181,6 @@ __global__ void dump_convert_kernel(const int2 *__restrict__ acc, int2 *__restri
     }
 }
 
-__global__ void scale2_kernel(const float *__restrict__ inv, float *__restrict__ s2, int C) {
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k < C) {
-        if (inv) {
-            const double x = (double)inv[k];
-            s2[k] = (float)(1.0 / (x * x));
-        } else {
-            s2[k] = 1.0f;
-        }
-    }
-}
-
 __global__ void dump_copy_kernel(const uint4 *__restrict__ acc, uint4 *__restrict__ dst, int64_t n_vec,
                                  const int *__restrict__ zflag) {
     const bool zero = *zflag != 0;
@@ -213,8 +204,8 @@ int grid_for(int64_t n) {
 // layout, so a public pointer advanced by k0 channels moves channels
 // [k0, k0 + nk) to held channels [0, nk).
 template <typename T, bool INGEST, bool SAT8 = false>
-hipError_t relayout_t(int C, int N, int n_spectra, SpecLayout lay, const void *src, void *dst, hipStream_t s,
-                      int nk = -1) {
+hipError_t relayout_t(int C, int N, int n_spectra, SpecLayout lay, const void *src, void *dst, UserScale us,
+                      hipStream_t s, int nk = -1) {
     constexpr int TB = kRowBytes / (int)sizeof(T);
     const int n_tb = (n_spectra + TB - 1) / TB;
     const int n_cc = (2 * N + kCols - 1) / kCols;
@@ -227,45 +218,45 @@ hipError_t relayout_t(int C, int N, int n_spectra, SpecLayout lay, const void *s
     uint8_t *out = static_cast<uint8_t *>(dst);
     if (vec)
         hipLaunchKernelGGL((relayout_kernel<T, INGEST, true, SAT8>), dim3((unsigned)grid), dim3(kThreads), 0, s, in,
-                           out, C, N, n_spectra, n_tb, n_cc, lay);
+                           out, C, N, n_spectra, n_tb, n_cc, lay, us);
     else
         hipLaunchKernelGGL((relayout_kernel<T, INGEST, false, SAT8>), dim3((unsigned)grid), dim3(kThreads), 0, s, in,
-                           out, C, N, n_spectra, n_tb, n_cc, lay);
+                           out, C, N, n_spectra, n_tb, n_cc, lay, us);
     return hipGetLastError();
 }
 
 }  // namespace
 
 hipError_t launch_ingest(int prec, int C, int N, int n_spectra, SpecLayout lay, const void *src, void *spec,
-                         hipStream_t stream) {
+                         UserScale us, hipStream_t stream) {
     switch (elem_bytes(prec)) {
-    case 4: return relayout_t<uint32_t, true>(C, N, n_spectra, lay, src, spec, stream);
-    case 2: return relayout_t<uint16_t, true>(C, N, n_spectra, lay, src, spec, stream);
+    case 4: return relayout_t<uint32_t, true>(C, N, n_spectra, lay, src, spec, us, stream);
+    case 2: return relayout_t<uint16_t, true>(C, N, n_spectra, lay, src, spec, us, stream);
     default:
-        if (prec == P_INT8) return relayout_t<uint8_t, true, true>(C, N, n_spectra, lay, src, spec, stream);
-        return relayout_t<uint8_t, true>(C, N, n_spectra, lay, src, spec, stream);
+        if (prec == P_INT8) return relayout_t<uint8_t, true, true>(C, N, n_spectra, lay, src, spec, us, stream);
+        return relayout_t<uint8_t, true>(C, N, n_spectra, lay, src, spec, us, stream);
     }
 }
 
 hipError_t launch_ingest_channels(int prec, int C, int k0, int nk, int N, int n_spectra, SpecLayout lay,
-                                  const void *src, void *spec, hipStream_t stream) {
+                                  const void *src, void *spec, UserScale us, hipStream_t stream) {
     if (k0 < 0 || nk < 1 || k0 + nk > C) return hipErrorInvalidValue;
     const uint8_t *s0 = static_cast<const uint8_t *>(src) + (int64_t)k0 * 2 * N * elem_bytes(prec);
     switch (elem_bytes(prec)) {
-    case 4: return relayout_t<uint32_t, true>(C, N, n_spectra, lay, s0, spec, stream, nk);
-    case 2: return relayout_t<uint16_t, true>(C, N, n_spectra, lay, s0, spec, stream, nk);
+    case 4: return relayout_t<uint32_t, true>(C, N, n_spectra, lay, s0, spec, us, stream, nk);
+    case 2: return relayout_t<uint16_t, true>(C, N, n_spectra, lay, s0, spec, us, stream, nk);
     default:
-        if (prec == P_INT8) return relayout_t<uint8_t, true, true>(C, N, n_spectra, lay, s0, spec, stream, nk);
-        return relayout_t<uint8_t, true>(C, N, n_spectra, lay, s0, spec, stream, nk);
+        if (prec == P_INT8) return relayout_t<uint8_t, true, true>(C, N, n_spectra, lay, s0, spec, us, stream, nk);
+        return relayout_t<uint8_t, true>(C, N, n_spectra, lay, s0, spec, us, stream, nk);
     }
 }
 
 hipError_t launch_export(int prec, int C, int N, int n_spectra, SpecLayout lay, const void *spec, void *dst,
                          hipStream_t stream) {
     switch (elem_bytes(prec)) {
-    case 4: return relayout_t<uint32_t, false>(C, N, n_spectra, lay, spec, dst, stream);
-    case 2: return relayout_t<uint16_t, false>(C, N, n_spectra, lay, spec, dst, stream);
-    default: return relayout_t<uint8_t, false>(C, N, n_spectra, lay, spec, dst, stream);
+    case 4: return relayout_t<uint32_t, false>(C, N, n_spectra, lay, spec, dst, UserScale{}, stream);
+    case 2: return relayout_t<uint16_t, false>(C, N, n_spectra, lay, spec, dst, UserScale{}, stream);
+    default: return relayout_t<uint8_t, false>(C, N, n_spectra, lay, spec, dst, UserScale{}, stream);
     }
 }
 
@@ -291,12 +282,6 @@ hipError_t launch_dump_copy(const void *acc, void *dst, int64_t n_words, const i
         e = hipGetLastError();
     }
     return e;
-}
-
-hipError_t launch_scale2(int C, const float *inv_scale, float *scale2, hipStream_t stream) {
-    hipLaunchKernelGGL(scale2_kernel, dim3((C + kThreads - 1) / kThreads), dim3(kThreads), 0, stream, inv_scale,
-                       scale2, C);
-    return hipGetLastError();
 }
 
 hipError_t launch_zero(void *p, int64_t n_words, hipStream_t stream) {

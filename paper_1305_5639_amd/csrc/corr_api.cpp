@@ -496,11 +496,10 @@ corr_status corr_fengine_at(corr_handle h, const void *d_volts, int64_t ld_sampl
     if (h->prec == P_INT8 && !d_inv_scale)
         return fail(h, CORR_E_INVALID_ARG, "int8 needs a per-channel scale");
 
-    hipError_t e = launch_scale2(h->C, d_inv_scale, h->scale2, h->stream);
-    if (e != hipSuccess) return hip_fail(h, e, "scale2 launch");
-    e = launch_fengine(h->prec, h->C, h->N, static_cast<const float2 *>(d_volts), ld_samples, n_spectra,
+    const hipError_t e = launch_fengine(h->prec, h->C, h->N, static_cast<const float2 *>(d_volts), ld_samples, n_spectra,
                        d_inv_scale ? d_inv_scale : h->unit_scale, h->twiddle, h->spec, h->lay,
-                       FScratch{h->gscr, h->gscr_bytes}, first_spectrum / time_block(h->prec), h->stream);
+                       FScratch{h->gscr, h->gscr_bytes}, first_spectrum / time_block(h->prec), h->scale2,
+                       h->stream);
     if (e != hipSuccess) return hip_fail(h, e, "fengine launch");
     h->n_held = first_spectrum + n_spectra;
     h->held_from_fengine = true;
@@ -527,11 +526,10 @@ corr_status corr_fengine_real8_at(corr_handle h, const int8_t *d_samples, int64_
     if (h->prec == P_INT8 && !d_inv_scale)
         return fail(h, CORR_E_INVALID_ARG, "int8 needs a per-channel scale");
 
-    hipError_t e = launch_scale2(h->C, d_inv_scale, h->scale2, h->stream);
-    if (e != hipSuccess) return hip_fail(h, e, "scale2 launch");
-    e = launch_fengine_real8(h->prec, h->C, h->N, d_samples, ld_samples, n_spectra,
+    const hipError_t e = launch_fengine_real8(h->prec, h->C, h->N, d_samples, ld_samples, n_spectra,
                              d_inv_scale ? d_inv_scale : h->unit_scale, h->twiddle, h->twiddle2n, h->spec,
-                             h->lay, FScratch{h->gscr, h->gscr_bytes}, first_spectrum / time_block(h->prec), h->stream);
+                             h->lay, FScratch{h->gscr, h->gscr_bytes}, first_spectrum / time_block(h->prec), h->scale2,
+                       h->stream);
     if (e != hipSuccess) return hip_fail(h, e, "fengine_real8 launch");
     h->n_held = first_spectrum + n_spectra;
     h->held_from_fengine = true;
@@ -564,15 +562,14 @@ corr_status corr_fx(corr_handle h, const void *d_volts, int64_t ld_samples, int3
     if (h->prec == P_INT8 && h->n_integrated + n_spectra > CORR_INT8_MAX_INTEGRATE)
         return fail(h, CORR_E_OVERFLOW, "int8 integration would exceed 66572 spectra since the last reset");
 
-    hipError_t e = launch_scale2(h->C, d_inv_scale, h->scale2, h->stream);
-    if (e != hipSuccess) return hip_fail(h, e, "scale2 launch");
+    hipError_t e = hipSuccess;
     const float2 *v = static_cast<const float2 *>(d_volts);
     int last = 0;
     for (int32_t s0 = 0; s0 < n_spectra; s0 += chunk_spectra) {
         const int ns = std::min(chunk_spectra, n_spectra - s0);
         e = launch_fengine(h->prec, h->C, h->N, v + (int64_t)s0 * h->C, ld_samples, ns,
                            d_inv_scale ? d_inv_scale : h->unit_scale, h->twiddle, h->spec, h->lay,
-                           FScratch{h->gscr, h->gscr_bytes}, 0, h->stream);
+                           FScratch{h->gscr, h->gscr_bytes}, 0, h->scale2, h->stream);
         if (e != hipSuccess) return hip_fail(h, e, "fengine launch");
         e = launch_xengine(h->prec, effective_tile(h), h->C, h->N, ns, h->spec, h->lay,
                            h->prec == P_INT8 ? nullptr : h->scale2, h->acc, h->acc, h->acc_zero ? 1 : 0, h->stream);
@@ -609,21 +606,16 @@ static corr_status prepare_x(corr_ctx *h, const void *d_spectra, int32_t n_spect
         return fail(h, CORR_E_OVERFLOW, "int8 integration would exceed 66572 spectra since the last reset");
 
     hipError_t e;
-    const float *s2 = nullptr;
+    float *s2 = nullptr;
     if (d_spectra) {
-        e = launch_ingest(h->prec, h->C, h->N, n_spectra, h->lay, d_spectra, h->spec, h->stream);
+        if (h->prec == P_FP16 || h->prec == P_FP8) s2 = h->scale2_user;
+        e = launch_ingest(h->prec, h->C, h->N, n_spectra, h->lay, d_spectra, h->spec,
+                          UserScale{d_inv_scale, s2, h->C}, h->stream);
         if (e != hipSuccess) return hip_fail(h, e, "ingest launch");
         h->n_held = n_spectra;
         h->held_from_fengine = false;
-        if (h->prec == P_FP16 || h->prec == P_FP8) {
-            e = launch_scale2(h->C, d_inv_scale, h->scale2_user, h->stream);
-            if (e != hipSuccess) return hip_fail(h, e, "scale2 launch");
-            s2 = h->scale2_user;
-        }
-    } else {
-        s2 = x_scale(h);
     }
-    *s2_out = s2;
+    *s2_out = d_spectra ? s2 : x_scale(h);
     return CORR_OK;
 }
 
@@ -909,7 +901,6 @@ corr_status corr_autotune_fx(corr_handle h, const void *d_volts, int64_t ld_samp
     const float2 *v = static_cast<const float2 *>(d_volts);
     h->n_held = 0;                                        // the spectra buffer is overwritten from here on
     h->held_from_fengine = false;
-    if ((e = launch_scale2(h->C, d_inv_scale, h->scale2, h->stream)) != hipSuccess) return hip_fail(h, e, "scale2");
     if (!cached) {
         // F-engine on every channel, X-engine on some of them into scratch
         // accumulators (the integration is untouched), scaled up to C
@@ -929,7 +920,7 @@ corr_status corr_autotune_fx(corr_handle h, const void *d_volts, int64_t ld_samp
                     e = hipEventRecord(ev[0], h->stream);
                     if (e == hipSuccess)
                         e = launch_fengine(h->prec, h->C, h->N, v, ld_samples, n_spectra, inv, h->twiddle, h->spec,
-                                           lay, FScratch{h->gscr, h->gscr_bytes}, 0, h->stream);
+                                           lay, FScratch{h->gscr, h->gscr_bytes}, 0, h->scale2, h->stream);
                     if (e == hipSuccess) e = hipEventRecord(ev[1], h->stream);
                     if (e == hipSuccess)
                         e = launch_xengine(h->prec, tile, Ct, h->N, n_spectra, h->spec, lay,
@@ -964,7 +955,7 @@ corr_status corr_autotune_fx(corr_handle h, const void *d_volts, int64_t ld_samp
     h->tb_major = best.tb_major == 1;
     h->lay = spec_layout_of(h->C, h->N, h->n_tb_cap, h->tb_major);
     e = launch_fengine(h->prec, h->C, h->N, v, ld_samples, n_spectra, inv, h->twiddle, h->spec, h->lay,
-                       FScratch{h->gscr, h->gscr_bytes}, 0, h->stream);
+                       FScratch{h->gscr, h->gscr_bytes}, 0, h->scale2, h->stream);
     if (e != hipSuccess) return hip_fail(h, e, "fengine launch");
     h->n_held = n_spectra;
     h->held_from_fengine = true;
@@ -1294,12 +1285,11 @@ corr_status corr_xengine_noalloc(const corr_params *params, const void *d_spectr
     float *s2 = static_cast<float *>(base);
     uint8_t *spec = static_cast<uint8_t *>(base) + s2_bytes;
     const bool scaled = prec == P_FP16 || prec == P_FP8;
-    if (scaled && (e = launch_scale2(C, d_inv_scale, s2, stream)) != hipSuccess)
-        return hip_fail(nullptr, e, "scale2 launch");
     const int64_t B = (int64_t)N * (N + 1) / 2;
     for (int k0 = 0; k0 < C; k0 += nk) {
         const int n = std::min(nk, C - k0);
-        e = launch_ingest_channels(prec, C, k0, n, N, n_spectra, lay, d_spectra, spec, stream);
+        e = launch_ingest_channels(prec, C, k0, n, N, n_spectra, lay, d_spectra, spec,
+                                   UserScale{d_inv_scale, scaled && k0 == 0 ? s2 : nullptr, C}, stream);
         if (e != hipSuccess) return hip_fail(nullptr, e, "ingest launch");
         uint8_t *vis = static_cast<uint8_t *>(d_vis) + (int64_t)k0 * B * 8;
         e = launch_xengine(prec, default_tile(prec, N, n), n, N, n_spectra, spec, lay, scaled ? s2 + k0 : nullptr, vis, vis,

@@ -68,6 +68,11 @@ inline int64_t spec_buffer_bytes(int C, int N, int n_tb_cap, int elem) {
     return most;
 }
 
+#ifdef __HIP__
+// s_k^2 = 1 / inv_s[k]^2
+__device__ __forceinline__ float square_of_scale(float inv) { return (float)(1.0 / ((double)inv * (double)inv)); }
+#endif
+
 inline int elem_bytes(int prec) { return prec == P_FP32 ? 4 : (prec == P_FP16 ? 2 : 1); }
 
 // From kGatherMinC channels on, an F-engine workgroup holds too few spectra
@@ -101,17 +106,18 @@ inline int time_block(int prec) { return kRowBytes / elem_bytes(prec); }
 // last block are written as zeros.  inv_scale: C floats, never null.  The
 // spectra land from time block first_tb of the buffer on.
 // From kGatherMinC channels on the call runs in chunks through scr (see
-// FScratch), one F-engine and one gather launch per chunk.
+// FScratch), one F-engine and one gather launch per chunk.  Also writes the
+// X-engine's s_k^2 = 1 / inv_s[k]^2 into scale2[C].
 hipError_t launch_fengine(int prec, int C, int N, const float2 *volts, int64_t ld,
                           int n_spectra, const float *inv_scale, const float2 *twiddle,
-                          void *spec, SpecLayout lay, FScratch scr, int first_tb, hipStream_t stream);
+                          void *spec, SpecLayout lay, FScratch scr, int first_tb, float *scale2, hipStream_t stream);
 
 // F-engine on int8 real samples (Section 5): block a of row p is the 2C bytes
 // samples[p*ld + a*2C ..]; channels k < C of its length-2C DFT.  twiddle2n[k]
 // = exp(-j pi k / C), k < C.  ld even.
 hipError_t launch_fengine_real8(int prec, int C, int N, const int8_t *samples, int64_t ld, int n_spectra,
                                 const float *inv_scale, const float2 *twiddle, const float2 *twiddle2n,
-                                void *spec, SpecLayout lay, FScratch scr, int first_tb, hipStream_t stream);
+                                void *spec, SpecLayout lay, FScratch scr, int first_tb, float *scale2, hipStream_t stream);
 
 // X-engine: accumulate Eq. 2 over the first n_spectra spectra of the spectra
 // buffer into acc (spectra past n_spectra in the last time block are masked to
@@ -179,16 +185,24 @@ struct XQueue {
 hipError_t launch_xengine_batched(int prec, const XQueue *d_plan, const XDesc *d_desc, int launch_group,
                                   unsigned int *counters, int num_cus, hipStream_t stream);
 
+// The scales of caller spectra: the ingest also writes scale2[k] = 1 / inv[k]^2
+// (1 where inv is null), k < C; nothing where scale2 is null.
+struct UserScale {
+    const float *inv;
+    float *scale2;
+    int C;
+};
+
 // Public [A][C][N][2] spectra <-> internal layout (ingest zero-fills the tail
 // of the last time block).
 hipError_t launch_ingest(int prec, int C, int N, int n_spectra, SpecLayout lay, const void *src,
-                         void *spec, hipStream_t stream);
+                         void *spec, UserScale us, hipStream_t stream);
 hipError_t launch_export(int prec, int C, int N, int n_spectra, SpecLayout lay, const void *spec,
                          void *dst, hipStream_t stream);
 // Ingest of channels [k0, k0 + nk) of public spectra with C channels into held
 // channels [0, nk) of spec (laid out by lay).
 hipError_t launch_ingest_channels(int prec, int C, int k0, int nk, int N, int n_spectra, SpecLayout lay,
-                                  const void *src, void *spec, hipStream_t stream);
+                                  const void *src, void *spec, UserScale us, hipStream_t stream);
 
 // Dump conversion from the lower-triangle channel-major accumulators into a
 // layout (0 lower, 1 upper, 2 full) and order (0 chan-major, 1 baseline-major).
@@ -200,9 +214,6 @@ hipError_t launch_dump_convert(int C, int N, int layout, int order, int is_int,
 
 // dst = acc (n_words 32-bit words), or zeros when *zflag is set.
 hipError_t launch_dump_copy(const void *acc, void *dst, int64_t n_words, const int *zflag, hipStream_t stream);
-
-// s_k^2 = 1 / inv_s[k]^2 (or 1 when inv_s is null) into scale2[C].
-hipError_t launch_scale2(int C, const float *inv_scale, float *scale2, hipStream_t stream);
 
 // Fill n 32-bit words with zero (a kernel, not a memset node, so the call is
 // safe inside captured graphs).
