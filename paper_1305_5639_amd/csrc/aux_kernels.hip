@@ -124,68 +124,126 @@ __global__ __launch_bounds__(kThreads) void relayout_kernel(const uint8_t *__res
     }
 }
 
-// Row i of the pair index for a flat index over the layout's pairs.
-__device__ __forceinline__ void pair_of(int layout, int N, int64_t b, int &i, int &j) {
-    if (layout == 2) {  // full
-        i = (int)(b / N);
-        j = (int)(b % N);
-    } else if (layout == 0) {  // lower: b = i(i+1)/2 + j
-        int r = (int)((sqrt(8.0 * (double)b + 1.0) - 1.0) * 0.5);
-        while ((int64_t)r * (r + 1) / 2 > b) --r;
-        while ((int64_t)(r + 1) * (r + 2) / 2 <= b) ++r;
-        i = r;
-        j = (int)(b - (int64_t)r * (r + 1) / 2);
-    } else {  // upper: b = i N - i(i-1)/2 + (j - i)
-        // row starts s(i) = i N - i(i-1)/2; find the largest i with s(i) <= b
-        const double Nd = N;
-        int r = (int)(((2.0 * Nd + 1.0) - sqrt((2.0 * Nd + 1.0) * (2.0 * Nd + 1.0) - 8.0 * (double)b)) * 0.5);
-        if (r < 0) r = 0;
-        if (r > N - 1) r = N - 1;
-        auto s = [&](int x) { return (int64_t)x * N - (int64_t)x * (x - 1) / 2; };
-        while (r > 0 && s(r) > b) --r;
-        while (r + 1 < N && s(r + 1) <= b) ++r;
-        i = r;
-        j = (int)(b - s(r)) + r;
-    }
+// Row and column of lower-triangle product b = i(i+1)/2 + j.
+__device__ __forceinline__ void pair_of(int64_t b, int &i, int &j) {
+    int r = (int)((sqrt(8.0 * (double)b + 1.0) - 1.0) * 0.5);
+    while ((int64_t)r * (r + 1) / 2 > b) --r;
+    while ((int64_t)(r + 1) * (r + 2) / 2 <= b) ++r;
+    i = r;
+    j = (int)(b - (int64_t)r * (r + 1) / 2);
 }
 
-__global__ void dump_convert_kernel(const int2 *__restrict__ acc, int2 *__restrict__ dst, int C, int N,
-                                    int layout, int order, int is_int, const int *__restrict__ zflag) {
+// Index of product (i, j), i <= j, in the upper triangle's rows.
+__device__ __forceinline__ int64_t upper_index(int N, int i, int j) {
+    return (int64_t)i * N - (int64_t)i * (i - 1) / 2 + (j - i);
+}
+
+// C_ji from C_ij.
+__device__ __forceinline__ int2 conj_of(int2 v, int is_int) {
+    return make_int2(v.x, is_int ? -v.y : __float_as_int(-__int_as_float(v.y)));
+}
+
+// The dump conversions read the accumulators once, in whole rows, and turn
+// them around in LDS, so that the writes are whole rows too.  Bound: HBM.  (One
+// thread per output element, dividing its index into a pair and reading the
+// accumulator there, against now: 300 inputs x 1024 channels full 0.51 -> 0.28 ms,
+// full baseline-major 1.04 -> 0.28; 256 x 1024 lower baseline-major 0.26 -> 0.13,
+// upper 0.29 -> 0.16; 1024 x 256 full 1.67 -> 0.59.)
+
+// Channel-major upper triangle or full matrix: a workgroup takes the products
+// of 32 rows I and 32 columns J <= I of one channel (gridDim.y: channels), the
+// mirrored ones through LDS.
+constexpr int kTile = 32;
+template <bool FULL>
+__global__ __launch_bounds__(kThreads) void dump_mirror_kernel(const int2 *__restrict__ acc, int2 *__restrict__ dst,
+                                                                int N, int is_int, const int *__restrict__ zflag) {
+    __shared__ int2 t[kTile][kTile + 1];
     const bool zero = zflag && *zflag;
     const int64_t Bl = (int64_t)N * (N + 1) / 2;
-    const int64_t Bt = layout == 2 ? (int64_t)N * N : Bl;
-    const int64_t total = Bt * C;
-    for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < total;
-         e += (int64_t)gridDim.x * blockDim.x) {
-        int64_t b;
-        int k;
-        if (order == 0) {
-            k = (int)(e / Bt);
-            b = e % Bt;
-        } else {
-            b = e / C;
-            k = (int)(e % C);
-        }
-        int i, j;
-        pair_of(layout, N, b, i, j);
-        const bool mirrored = j > i;
-        const int ii = mirrored ? j : i, jj = mirrored ? i : j;
-        int2 v = zero ? make_int2(0, 0) : acc[(int64_t)k * Bl + (int64_t)ii * (ii + 1) / 2 + jj];
-        if (mirrored) {  // C_ij = conj(C_ji)
-            if (is_int)
-                v.y = -v.y;
-            else
-                v.y = __float_as_int(-__int_as_float(v.y));
-        }
-        dst[e] = v;
+    const int k = blockIdx.y;
+    int bi, bj;
+    pair_of(blockIdx.x, bi, bj);
+    const int x = threadIdx.x % kTile, y0 = threadIdx.x / kTile;
+    const int2 *src = acc + k * Bl;
+    int2 *out = dst + k * (FULL ? (int64_t)N * N : Bl);
+    constexpr int R = kTile * kTile / kThreads;        // products per thread
+    int2 v[R];                                         // (read together: places outside read product 0)
+#pragma unroll
+    for (int q = 0; q < R; ++q) {
+        const int i = bi * kTile + y0 + q * (kThreads / kTile), j = bj * kTile + x;
+        v[q] = src[i < N && j <= i ? (int64_t)i * (i + 1) / 2 + j : 0];
+    }
+#pragma unroll
+    for (int q = 0; q < R; ++q) {
+        const int y = y0 + q * (kThreads / kTile), i = bi * kTile + y, j = bj * kTile + x;
+        if (zero) v[q] = make_int2(0, 0);
+        t[y][x] = v[q];
+        if (FULL && i < N && j <= i) out[(int64_t)i * N + j] = v[q];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int y = y0; y < kTile; y += kThreads / kTile) {
+        const int i = bi * kTile + x, j = bj * kTile + y;   // product (j, i) of the upper triangle
+        if (i >= N || j > i || (FULL && j == i)) continue;
+        out[FULL ? (int64_t)j * N + i : upper_index(N, j, i)] = i == j ? t[x][y] : conj_of(t[x][y], is_int);
     }
 }
 
-__global__ void dump_copy_kernel(const uint4 *__restrict__ acc, uint4 *__restrict__ dst, int64_t n_vec,
+// Baseline-major dumps, in any layout: a workgroup takes 64 products of 32
+// channels.
+constexpr int kProducts = 64;
+__global__ __launch_bounds__(kThreads) void dump_baseline_kernel(const int2 *__restrict__ acc, int2 *__restrict__ dst,
+                                                                  int C, int N, int layout, int is_int,
+                                                                  const int *__restrict__ zflag) {
+    __shared__ int2 t[kTile][kProducts + 1];
+    __shared__ int pi[kProducts], pj[kProducts];
+    const bool zero = zflag && *zflag;
+    const int64_t Bl = (int64_t)N * (N + 1) / 2;
+    const int64_t b0 = (int64_t)blockIdx.x * kProducts;
+    const int k0 = blockIdx.y * kTile;
+    {
+        constexpr int R = kTile * kProducts / kThreads;   // products per thread
+        const int x = threadIdx.x % kProducts, y0 = threadIdx.x / kProducts;
+        int2 v[R];                                     // (read together: places outside read product 0)
+#pragma unroll
+        for (int q = 0; q < R; ++q) {
+            const int k = k0 + y0 + q * (kThreads / kProducts);
+            v[q] = acc[b0 + x < Bl && k < C ? k * Bl + b0 + x : 0];
+        }
+        if (layout != 0 && threadIdx.x < kProducts && b0 + threadIdx.x < Bl)
+            pair_of(b0 + threadIdx.x, pi[threadIdx.x], pj[threadIdx.x]);
+#pragma unroll
+        for (int q = 0; q < R; ++q) t[y0 + q * (kThreads / kProducts)][x] = zero ? make_int2(0, 0) : v[q];
+    }
+    __syncthreads();
+    const int x = threadIdx.x % kTile;
+    if (k0 + x >= C) return;
+#pragma unroll
+    for (int y = threadIdx.x / kTile; y < kProducts; y += kThreads / kTile) {
+        if (b0 + y >= Bl) break;
+        const int2 v = t[x][y];
+        if (layout == 0) {
+            dst[(b0 + y) * C + k0 + x] = v;
+            continue;
+        }
+        const int i = pi[y], j = pj[y];
+        const int2 w = i == j ? v : conj_of(v, is_int);
+        if (layout == 1) {
+            dst[upper_index(N, j, i) * C + k0 + x] = w;
+        } else {
+            dst[((int64_t)i * N + j) * C + k0 + x] = v;
+            if (i != j) dst[((int64_t)j * N + i) * C + k0 + x] = w;
+        }
+    }
+}
+
+// dst = src, n elements, or zeros where *zflag is set.
+template <typename V>
+__global__ void dump_copy_kernel(const V *__restrict__ src, V *__restrict__ dst, int64_t n,
                                  const int *__restrict__ zflag) {
-    const bool zero = *zflag != 0;
-    for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n_vec; e += (int64_t)gridDim.x * blockDim.x)
-        dst[e] = zero ? make_uint4(0, 0, 0, 0) : acc[e];
+    const bool zero = zflag && *zflag;
+    for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += (int64_t)gridDim.x * blockDim.x)
+        dst[e] = zero ? V{} : src[e];
 }
 
 __global__ void zero_kernel(uint32_t *__restrict__ p, int64_t n) {
@@ -262,26 +320,31 @@ hipError_t launch_export(int prec, int C, int N, int n_spectra, SpecLayout lay, 
 
 hipError_t launch_dump_convert(int C, int N, int layout, int order, int is_int, const void *acc, void *dst,
                                hipStream_t stream, const int *zflag) {
-    const int64_t Bt = layout == 2 ? (int64_t)N * N : (int64_t)N * (N + 1) / 2;
-    hipLaunchKernelGGL(dump_convert_kernel, dim3(grid_for(Bt * C)), dim3(kThreads), 0, stream,
-                       static_cast<const int2 *>(acc), static_cast<int2 *>(dst), C, N, layout, order, is_int, zflag);
+    const int2 *a = static_cast<const int2 *>(acc);
+    int2 *d = static_cast<int2 *>(dst);
+    const int64_t Bl = (int64_t)N * (N + 1) / 2, n = (N + kTile - 1) / kTile;
+    if (order != 0) {
+        const dim3 grid((unsigned)((Bl + kProducts - 1) / kProducts), (unsigned)((C + kTile - 1) / kTile));
+        hipLaunchKernelGGL(dump_baseline_kernel, grid, dim3(kThreads), 0, stream, a, d, C, N, layout, is_int, zflag);
+    } else if (layout == 0) {
+        hipLaunchKernelGGL(dump_copy_kernel<int2>, dim3(grid_for(Bl * C)), dim3(kThreads), 0, stream, a, d, Bl * C,
+                           zflag);
+    } else if (layout == 1) {
+        hipLaunchKernelGGL(dump_mirror_kernel<false>, dim3((unsigned)(n * (n + 1) / 2), (unsigned)C), dim3(kThreads), 0,
+                           stream, a, d, N, is_int, zflag);
+    } else {
+        hipLaunchKernelGGL(dump_mirror_kernel<true>, dim3((unsigned)(n * (n + 1) / 2), (unsigned)C), dim3(kThreads), 0,
+                           stream, a, d, N, is_int, zflag);
+    }
     return hipGetLastError();
 }
 
 hipError_t launch_dump_copy(const void *acc, void *dst, int64_t n_words, const int *zflag, hipStream_t stream) {
-    // accumulators are 8-byte pairs, C * B of them; copy as 16-byte vectors
-    // and finish an odd pair with the zero flag as a 2-word tail
-    const int64_t n_vec = n_words / 4;
-    hipLaunchKernelGGL(dump_copy_kernel, dim3(grid_for(n_vec)), dim3(kThreads), 0, stream,
-                       static_cast<const uint4 *>(acc), static_cast<uint4 *>(dst), n_vec, zflag);
-    hipError_t e = hipGetLastError();
-    if (e == hipSuccess && n_words % 4) {
-        hipLaunchKernelGGL(dump_convert_kernel, dim3(1), dim3(kThreads), 0, stream,
-                           static_cast<const int2 *>(acc) + 2 * n_vec, static_cast<int2 *>(dst) + 2 * n_vec,
-                           1, 1, 0, 0, 0, zflag);
-        e = hipGetLastError();
-    }
-    return e;
+    // accumulators are 8-byte pairs, C * B of them (C even): 16-byte vectors
+    if (n_words % 4) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(dump_copy_kernel<int4>, dim3(grid_for(n_words / 4)), dim3(kThreads), 0, stream,
+                       static_cast<const int4 *>(acc), static_cast<int4 *>(dst), n_words / 4, zflag);
+    return hipGetLastError();
 }
 
 hipError_t launch_zero(void *p, int64_t n_words, hipStream_t stream) {
