@@ -192,6 +192,35 @@ __device__ __forceinline__ int lidx(int t, int i) {
     return t * (C + (C >> P::SH) + P::EX) + i + (i >> P::SH);
 }
 
+// The same for fields that share no bits: the padding of their sum is the sum
+// of their paddings.  Everything a thread reads or writes in LDS then lies at
+// one place that its index gives (at) plus compile-time offsets (step), which
+// are immediates of the LDS instructions; left to itself the compiler shifts
+// and masks anew for each element (250-300 of the 2000 vector instructions of a
+// thread at 2048 and 4096 channels).
+template <int C> __device__ __forceinline__ constexpr int pad(int x) { return x + (x >> Plan<C>::SH); }
+template <int C> constexpr int row_stride() { return pad<C>(C) + Plan<C>::EX; }
+
+// Element j + r C/R of spectrum t, (t, j) = butterfly b = tid + TH q by MAP_PLAIN
+// or MAP_REMAP.
+template <int C, int T, int TH, int R, int MAP> struct ReadAt {
+    static_assert(MAP != MAP_PAIRED, "mirrored indices are not sums");
+    static __device__ __forceinline__ constexpr int t_of(int b) { return MAP == MAP_REMAP ? b % T : b / (C / R); }
+    static __device__ __forceinline__ constexpr int j_of(int b) { return MAP == MAP_REMAP ? b / T : b % (C / R); }
+    static __device__ __forceinline__ constexpr int at(int b) { return t_of(b) * row_stride<C>() + pad<C>(j_of(b)); }
+    static __device__ __forceinline__ constexpr int step(int q, int r) { return at(TH * q) + pad<C>(r * (C / R)); }
+};
+
+// Element (j/NS) NS R + j mod NS + r NS of spectrum t, (t, j) = butterfly
+// tid + TH q by MAP_PLAIN.
+template <int C, int T, int TH, int R, int NS> struct WriteAt {
+    static __device__ __forceinline__ constexpr int at(int b) {
+        const int j = b % (C / R);
+        return b / (C / R) * row_stride<C>() + pad<C>(j / NS * NS * R) + pad<C>(j % NS);
+    }
+    static __device__ __forceinline__ constexpr int step(int q, int r) { return at(TH * q) + pad<C>(r * NS); }
+};
+
 // First Stockham pass, radix R: butterfly (t, j) takes x[t][j + r C/R] straight
 // from global memory (spectra past n_spectra read as zero) and does an R-point
 // DFT; no twiddles precede the first pass.  The loads are unconditional (a
@@ -279,26 +308,51 @@ __device__ __forceinline__ void later_pass(float2 *v, const float2 *__restrict__
 template <int C, int T, int TH, int R1, int NS1, int R2, int MAP2, bool SPLIT>
 __device__ __forceinline__ void exchange(float2 *v, float *lds, int tid, bool wait_first) {
     constexpr int PT = T * C / TH;
-    constexpr int Q1 = PT / R1, Q2 = PT / R2, CR2 = C / R2;
+    constexpr int Q1 = PT / R1, Q2 = PT / R2;
+    // Sums of a place and an immediate (see pad), except with whole complex
+    // values in three passes, where they let the compiler join LDS reads in
+    // pairs of 8 bytes, which were slower (FP32 8192 channels 1.02 -> 1.14 ms,
+    // 4096 3.86 -> 4.0), and mirrored indices, which are no sums.
+    constexpr bool SUMS = SPLIT || Plan<C>::NP < 3;
+    using W = WriteAt<C, T, TH, R1, NS1>;
+    const int w0 = W::at(tid);
+    // where element (q, r) goes
+    auto here = [&](int q, int r) {
+        if constexpr (!SUMS) {
+            int t, j;
+            bfly_index<C, T, TH, R1, MAP_PLAIN>(tid, q, t, j);
+            return lidx<C>(t, (j / NS1) * NS1 * R1 + (j % NS1) + r * NS1);
+        } else {
+            return w0 + W::step(q, r);
+        }
+    };
+    // where the next pass's element (q, r) lies
+    auto next = [&](int q, int r) {
+        if constexpr (!SUMS) {
+            int t, j;
+            bfly_index<C, T, TH, R2, MAP2>(tid, q, t, j);
+            return lidx<C>(t, j + r * (C / R2));
+        } else if constexpr (MAP2 == MAP_PAIRED) {
+            int t, j;
+            bfly_index<C, T, TH, R2, MAP2>(tid, q, t, j);
+            return lidx<C>(t, j) + pad<C>(r * (C / R2));
+        } else {
+            using N = ReadAt<C, T, TH, R2, MAP2>;
+            return N::at(tid) + N::step(q, r);
+        }
+    };
     if constexpr (!SPLIT) {
         float2 *l2 = reinterpret_cast<float2 *>(lds);
         if (wait_first) __syncthreads();
 #pragma unroll
-        for (int q = 0; q < Q1; ++q) {
-            int t, j;
-            bfly_index<C, T, TH, R1, MAP_PLAIN>(tid, q, t, j);
-            const int base = (j / NS1) * NS1 * R1 + (j % NS1);
+        for (int q = 0; q < Q1; ++q)
 #pragma unroll
-            for (int r = 0; r < R1; ++r) l2[lidx<C>(t, base + r * NS1)] = v[q * R1 + r];
-        }
+            for (int r = 0; r < R1; ++r) l2[here(q, r)] = v[q * R1 + r];
         __syncthreads();
 #pragma unroll
-        for (int q = 0; q < Q2; ++q) {
-            int t, j;
-            bfly_index<C, T, TH, R2, MAP2>(tid, q, t, j);
+        for (int q = 0; q < Q2; ++q)
 #pragma unroll
-            for (int r = 0; r < R2; ++r) v[q * R2 + r] = l2[lidx<C>(t, j + r * CR2)];
-        }
+            for (int r = 0; r < R2; ++r) v[q * R2 + r] = l2[next(q, r)];
         return;
     }
     float xr[PT];
@@ -306,25 +360,18 @@ __device__ __forceinline__ void exchange(float2 *v, float *lds, int tid, bool wa
     for (int comp = 0; comp < 2; ++comp) {
         if (comp == 1 || wait_first) __syncthreads();
 #pragma unroll
-        for (int q = 0; q < Q1; ++q) {
-            int t, j;
-            bfly_index<C, T, TH, R1, MAP_PLAIN>(tid, q, t, j);
-            const int base = (j / NS1) * NS1 * R1 + (j % NS1);
+        for (int q = 0; q < Q1; ++q)
 #pragma unroll
-            for (int r = 0; r < R1; ++r) lds[lidx<C>(t, base + r * NS1)] = comp ? v[q * R1 + r].y : v[q * R1 + r].x;
-        }
+            for (int r = 0; r < R1; ++r) lds[here(q, r)] = comp ? v[q * R1 + r].y : v[q * R1 + r].x;
         __syncthreads();
 #pragma unroll
-        for (int q = 0; q < Q2; ++q) {
-            int t, j;
-            bfly_index<C, T, TH, R2, MAP2>(tid, q, t, j);
+        for (int q = 0; q < Q2; ++q)
 #pragma unroll
             for (int r = 0; r < R2; ++r) {
-                const float e = lds[lidx<C>(t, j + r * CR2)];
+                const float e = lds[next(q, r)];
                 if (comp == 0) xr[q * R2 + r] = e;
                 else v[q * R2 + r] = make_float2(xr[q * R2 + r], e);
             }
-        }
     }
 }
 
