@@ -39,13 +39,13 @@ namespace corr {
 namespace {
 
 // The complex FP32 form at 2048 and 4096 channels stores straight into the
-// held rows from 512-thread workgroups (8 or 4 spectra each, so 32- or
-// 16-byte pieces of each row) instead of through the chunked gather: on 2^28
-// samples 1.83 -> 1.64 ms at 2048 and 2.05 -> 1.93 ms at 4096 channels, and
-// 30.7 -> 28.6 ms for 1024 inputs x 4096 channels x 1024 spectra.  At 8192
-// channels (2 spectra per workgroup) the gather stays faster (2.36 against
-// 2.94 ms), and so it does for every low-precision form, whose larger
-// workgroups measured 35-75% slower.
+// held rows (in 16-byte pieces of each) instead of through the chunked gather:
+// 2048 channels from 256-thread workgroups, two per CU (1024 inputs x 512
+// spectra: 5.1 ms; one 512-thread workgroup per CU with 32-byte pieces 6.4; the
+// gather 7.1-7.8), 4096 channels from 512-thread ones (512 x 256: 3.8 ms; 256
+// threads with 8-byte pieces 5.8; the gather 4.2).  At 8192 channels (1 or 2
+// spectra per workgroup) the gather stays faster, and so it does for every
+// low-precision form, whose larger workgroups measured 35-75% slower.
 template <int C, int PREC, bool REAL>
 constexpr bool fp32_direct() {
     return !REAL && PREC == P_FP32 && (C == 2048 || C == 4096);
@@ -54,11 +54,11 @@ constexpr bool fp32_direct() {
 // Threads per workgroup: 256, or 512 for the int8 / FP8 complex forms at C =
 // 512 and 1024, where twice the spectra per workgroup (so half as many
 // partial output rows) measured 3-10% faster on 2^28 samples; at 256 channels
-// they gained nothing; and 512 for fp32_direct.  From 2048 channels the
+// they gained nothing; and for fp32_direct as said there.  From 2048 channels the
 // chunked store and gather leave no partial rows to save.
 template <int C, int PREC, bool REAL>
 constexpr int threads() {
-    if (fp32_direct<C, PREC, REAL>()) return 512;
+    if (fp32_direct<C, PREC, REAL>()) return C == 2048 ? 256 : 512;
     return (!REAL && (PREC == P_INT8 || PREC == P_FP8) && (C == 512 || C == 1024)) ? 512 : 256;
 }
 
