@@ -516,33 +516,45 @@ __device__ __forceinline__ void real_split_lds(float2 *v, float *lds, const floa
 }
 
 // ---- requantisation --------------------------------------------------------
-// OCP E4M3 (gfx950's FP8 format), round half to even, saturating at +-448: the
-// value is clamped to the largest finite E4M3 magnitude first, so the
-// hardware conversion (round to nearest even) never overflows.
-__device__ __forceinline__ uint8_t to_e4m3(float y) {
-    y = fminf(fmaxf(y, -448.0f), 448.0f);
-    return (uint8_t)(__builtin_amdgcn_cvt_pk_fp8_f32(y, y, 0, false) & 0xff);
-}
-
-template <int PREC> struct Elem;
-template <> struct Elem<P_FP32> {
-    using T = float;
-    static __device__ __forceinline__ T conv(float y) { return y; }
+// Both parts of a spectrum value, scaled, as the pair of elements (re low) that
+// is staged.
+template <int PREC> struct Pair;
+template <> struct Pair<P_FP32> {
+    using T = float2;
+    static constexpr int ES = 4;
+    static __device__ __forceinline__ T conv(float re, float im) { return make_float2(re, im); }
 };
-template <> struct Elem<P_FP16> {
-    using T = _Float16;
-    static __device__ __forceinline__ T conv(float y) {
-        return (_Float16)fminf(fmaxf(y, -65504.0f), 65504.0f);   // RNE, saturating
+template <> struct Pair<P_FP16> {
+    using T = uint32_t;
+    static constexpr int ES = 2;
+    static __device__ __forceinline__ T conv(float re, float im) {
+        typedef _Float16 h2 __attribute__((ext_vector_type(2)));   // RNE, saturating
+        return __builtin_bit_cast(uint32_t, h2{(_Float16)fminf(fmaxf(re, -65504.0f), 65504.0f),
+                                               (_Float16)fminf(fmaxf(im, -65504.0f), 65504.0f)});
     }
 };
-template <> struct Elem<P_FP8> {
-    using T = uint8_t;
-    static __device__ __forceinline__ T conv(float y) { return to_e4m3(y); }
+// OCP E4M3 (gfx950's FP8 format), round half to even, saturating at +-448: the
+// values are clamped to the largest finite E4M3 magnitude first, so the
+// hardware conversion (round to nearest even) never overflows.
+template <> struct Pair<P_FP8> {
+    using T = uint16_t;
+    static constexpr int ES = 1;
+    static __device__ __forceinline__ T conv(float re, float im) {
+        re = fminf(fmaxf(re, -448.0f), 448.0f);
+        im = fminf(fmaxf(im, -448.0f), 448.0f);
+        return (uint16_t)__builtin_amdgcn_cvt_pk_fp8_f32(re, im, 0, false);
+    }
 };
-template <> struct Elem<P_INT8> {
-    using T = int8_t;
-    static __device__ __forceinline__ T conv(float y) {
-        return (int8_t)fminf(fmaxf(rintf(y), -127.0f), 127.0f);  // RNE, symmetric clamp
+// Round half to even, symmetric clamp.  Added to 1.5 * 2^23 a clamped value is
+// rounded so, and the sum's low byte is the integer.
+template <> struct Pair<P_INT8> {
+    using T = uint16_t;
+    static constexpr int ES = 1;
+    static __device__ __forceinline__ uint32_t bits(float y) {
+        return __float_as_uint(fminf(fmaxf(y, -127.0f), 127.0f) + 12582912.0f);
+    }
+    static __device__ __forceinline__ T conv(float re, float im) {
+        return (uint16_t)__builtin_amdgcn_perm(bits(im), bits(re), 0x0c0c0400u);
     }
 };
 
@@ -552,6 +564,26 @@ template <> struct Bytes<2> { using T = uint16_t; };
 template <> struct Bytes<4> { using T = uint32_t; };
 template <> struct Bytes<8> { using T = uint2; };
 template <> struct Bytes<16> { using T = uint4; };
+
+// Word d of plane pl's elements of N pairs of ES bytes each that lie in the
+// words w(i): pair e (e < N) in bytes [2 ES pos(e), +2 ES) of them.
+template <int ES, typename Words, typename Pos>
+__device__ __forceinline__ uint32_t plane_word(const Words &w, const Pos &pos, int pl, int d) {
+    if constexpr (ES == 4) {
+        return w(2 * pos(d) + pl);
+    } else if constexpr (ES == 2) {
+        return __builtin_amdgcn_perm(w(pos(2 * d + 1)), w(pos(2 * d)), pl ? 0x07060302u : 0x05040100u);
+    } else {
+        const int e0 = pos(4 * d), e1 = pos(4 * d + 1), e2 = pos(4 * d + 2), e3 = pos(4 * d + 3);
+        if (e0 / 2 == e1 / 2 && e2 / 2 == e3 / 2)      // (a word holds two pairs)
+            return __builtin_amdgcn_perm(w(e2 / 2), w(e0 / 2), pl ? 0x07050301u : 0x06040200u);
+        const uint32_t b0 = 2 * (e0 & 1) + pl, b1 = 4 + 2 * (e1 & 1) + pl, b2 = 2 * (e2 & 1) + pl,
+                       b3 = 4 + 2 * (e3 & 1) + pl;
+        const uint32_t lo = __builtin_amdgcn_perm(w(e1 / 2), w(e0 / 2), b0 | b1 << 8 | 0x0c0c0000u);
+        const uint32_t hi = __builtin_amdgcn_perm(w(e3 / 2), w(e2 / 2), b2 | b3 << 8 | 0x0c0c0000u);
+        return __builtin_amdgcn_perm(hi, lo, 0x05040100u);
+    }
+}
 
 // REAL: the input is int8 real samples (ld in bytes, block a at byte a*2C of
 // its row) and tw2 holds exp(-j pi k / C); otherwise complex64 voltages (ld in
@@ -564,7 +596,7 @@ __global__ __launch_bounds__((threads<C, PREC, REAL>())) __attribute__((amdgpu_w
     int n_work, const float *__restrict__ inv_scale,
     const float2 *__restrict__ tw, const float2 *__restrict__ tw2, uint8_t *__restrict__ spec, int64_t k_stride,
     int64_t t_stride, int tb0, float *__restrict__ scale2) {
-    using E = typename Elem<PREC>::T;
+    using PR = Pair<PREC>;
     constexpr int TH = threads<C, PREC, REAL>();      // threads per workgroup
     constexpr int PT = per_thread<C, PREC, REAL>();   // complex values per thread
     constexpr int T = TH * PT / C;                     // spectra per workgroup
@@ -573,7 +605,7 @@ __global__ __launch_bounds__((threads<C, PREC, REAL>())) __attribute__((amdgpu_w
     constexpr int RL = Last<C>::RL;                    // last radix
     constexpr int LMAP = REAL && Last<C>::PAIRED ? MAP_PAIRED : MAP_REMAP;
     constexpr int CP = C + (C >> P::SH) + P::EX;       // LDS row stride (floats)
-    constexpr int ES = (int)sizeof(E);
+    constexpr int ES = PR::ES;
     constexpr int TB = kRowBytes / ES;                 // spectra per time block
     constexpr int S = T * ES;                          // bytes of one staged row
     constexpr int CH = S < 16 ? S : 16;                // store chunk
@@ -604,8 +636,7 @@ __global__ __launch_bounds__((threads<C, PREC, REAL>())) __attribute__((amdgpu_w
     constexpr bool GATHER = C >= kGatherMinC && !fp32_direct<C, PREC, REAL>();
     static_assert(!GATHER || T <= TB, "a gathered workgroup must lie within one time block");
     constexpr int LF = SPLIT ? 1 : 2;                  // floats per LDS element
-    constexpr int NPL = 2 * C * S <= T * CP * 4 * LF ? 2 : 1;   // planes staged at a time
-    static_assert(NPL * C * S <= T * CP * 4 * LF, "staging must fit the FFT buffer");
+    static_assert(2 * C * S <= T * CP * 4 * LF, "staging must fit the FFT buffer");
 
     __shared__ __attribute__((aligned(16))) float lds[T * CP * LF];
     const int tid = threadIdx.x;
@@ -639,110 +670,111 @@ __global__ __launch_bounds__((threads<C, PREC, REAL>())) __attribute__((amdgpu_w
     }
 
     // v[q RL + r] holds channel k = j + r C/RL of spectrum t for last-pass
-    // butterfly q, (t, j) as mapping LMAP gives them.  NPL planes at a time
-    // are requantised and staged in LDS as [plane][channel][spectrum], then
-    // stored as runs of consecutive spectra of each (channel, plane) row:
-    // the row (k, tb, p, plane) at spec + tb t_stride + k k_stride + p 128 +
-    // plane 64, or, for GATHER, the workgroup's staged block as it stands.
+    // butterfly q, (t, j) as mapping LMAP gives them.  The values are requantised
+    // and staged in LDS as pairs, [channel][spectrum][part]: one conversion and
+    // one LDS write for both parts where they had two (2048 channels int8 5.87 ->
+    // 5.72 ms with the gather, 64 channels FP32 0.29 -> 0.24, 4096 FP32 3.70 -> 3.42,
+    // 8192 FP16 0.37 -> 0.33).  From there they go as runs
+    // of consecutive spectra to the rows (k, tb, p, plane) at spec + tb t_stride +
+    // k k_stride + p 128 + plane 64, or, for GATHER, as the staged block stands.
     constexpr int CR = C / RL;
-    using V = typename Bytes<CH>::T;
-    constexpr int CPR = S / CH;                        // chunks per staged row
-    constexpr int NCH = NPL * C * CPR;
+    using PT2 = typename PR::T;
     uint8_t *stage = reinterpret_cast<uint8_t *>(lds);
+    __syncthreads();                                   // every thread is done reading lds
 #pragma unroll
-    for (int pl0 = 0; pl0 < 2; pl0 += NPL) {
-        __syncthreads();                               // every thread is done reading lds
+    for (int q = 0; q < PT / RL; ++q) {
+        int t, j;
+        bfly_index<C, T, TH, RL, LMAP>(tid, q, t, j);
 #pragma unroll
-        for (int q = 0; q < PT / RL; ++q) {
-            int t, j;
-            bfly_index<C, T, TH, RL, LMAP>(tid, q, t, j);
-#pragma unroll
-            for (int r = 0; r < RL; ++r) {
-                const int k = j + r * CR;
-                const float sc = SCALE_TEST ? (inv_scale ? inv_scale[k] : 1.0f) : inv_scale[k];
-                const float2 y = v[q * RL + r];
-#pragma unroll
-                for (int pp = 0; pp < NPL; ++pp)
-                    *reinterpret_cast<E *>(stage + (pp * C + k) * S + t * ES) =
-                        Elem<PREC>::conv((pl0 + pp ? y.y : y.x) * sc);
-            }
+        for (int r = 0; r < RL; ++r) {
+            const int k = j + r * CR;
+            const float sc = SCALE_TEST ? (inv_scale ? inv_scale[k] : 1.0f) : inv_scale[k];
+            const float2 y = v[q * RL + r];
+            *reinterpret_cast<PT2 *>(stage + (k * T + t) * (2 * ES)) = PR::conv(y.x * sc, y.y * sc);
         }
-        __syncthreads();
-        for (int c = tid; c < NCH; c += TH) {
-            const int row = c / CPR, x = c % CPR;
-            const int pl = pl0 + row / C, k = row % C;
-            const int a = a0 + x * (CH / ES);
+    }
+    __syncthreads();
+    if constexpr (GATHER) {
+        uint4 *dst = reinterpret_cast<uint4 *>(spec + (int64_t)w * (2 * C * S));
+        for (int c = tid; c < 2 * C * S / 16; c += TH)
+            if (a0 < n_valid_pad) dst[c] = reinterpret_cast<const uint4 *>(stage)[c];
+    } else {
+        using V = typename Bytes<CH>::T;
+        constexpr int CPR = S / CH;                    // chunks per staged row
+        for (int c = tid; c < C * CPR; c += TH) {
+            const int k = c / CPR, a = a0 + c % CPR * (CH / ES);
             if (a >= n_valid_pad) continue;
-            const int tb = tb0 + a / TB, within = a % TB;
-            uint8_t *dst = GATHER ? spec + (int64_t)w * (2 * C * S) + (int64_t)pl0 * C * S + (int64_t)c * CH
-                                  : spec + (int64_t)tb * t_stride + (int64_t)k * k_stride +
-                                        (int64_t)p * (2 * kRowBytes) + pl * kRowBytes + within * ES;
-            *reinterpret_cast<V *>(dst) = *reinterpret_cast<const V *>(stage + c * CH);
+            uint32_t u[CH / 2], o[2][CH / 4];          // CH / ES pairs; their planes
+            __builtin_memcpy(u, stage + c * 2 * CH, 2 * CH);
+#pragma unroll
+            for (int pl = 0; pl < 2; ++pl)
+#pragma unroll
+                for (int d = 0; d < CH / 4; ++d)
+                    o[pl][d] = plane_word<ES>([&](int i) { return u[i]; }, [](int e) { return e; }, pl, d);
+            uint8_t *dst = spec + (int64_t)(tb0 + a / TB) * t_stride + (int64_t)k * k_stride +
+                           (int64_t)p * (2 * kRowBytes) + a % TB * ES;
+            V x;
+            __builtin_memcpy(&x, o[0], CH);
+            *reinterpret_cast<V *>(dst) = x;
+            __builtin_memcpy(&x, o[1], CH);
+            *reinterpret_cast<V *>(dst + kRowBytes) = x;
         }
     }
 }
 
-// Transpose of PV = 16 / S vectors of 16 bytes, each PV pieces of S bytes, in
-// registers: out[j] = piece j of in[0], in[1], ...
-template <int S>
-__device__ __forceinline__ void transpose_pieces(const uint4 (&in)[16 / S], uint4 (&out)[16 / S]) {
-    constexpr int PV = 16 / S;
-    uint32_t a[PV][4], o[PV][4];
-    __builtin_memcpy(a, in, sizeof a);
-#pragma unroll
-    for (int j = 0; j < PV; ++j)
-#pragma unroll
-        for (int d = 0; d < 4; ++d) {
-            if constexpr (S >= 4) {                    // whole words
-                constexpr int W = S / 4;               // words of a piece
-                o[j][d] = a[d / W][j * W + d % W];
-            } else if constexpr (S == 2) {             // halves of pieces 2 d and 2 d + 1
-                const uint32_t sel = j & 1 ? 0x07060302u : 0x05040100u;
-                o[j][d] = __builtin_amdgcn_perm(a[2 * d + 1][j / 2], a[2 * d][j / 2], sel);
-            } else {                                   // bytes of pieces 4 d .. 4 d + 3
-                const uint32_t b = j & 3, sel = b | (4 + b) << 8 | 0x0c0c0000u;
-                const uint32_t lo = __builtin_amdgcn_perm(a[4 * d + 1][j / 4], a[4 * d][j / 4], sel);
-                const uint32_t hi = __builtin_amdgcn_perm(a[4 * d + 3][j / 4], a[4 * d + 2][j / 4], sel);
-                o[j][d] = __builtin_amdgcn_perm(hi, lo, 0x05040100u);
-            }
-        }
-    __builtin_memcpy(out, o, sizeof o);
-}
-
 // Second step of a gathered F-engine chunk: the scratch holds, for chunk time
-// block tbl, chunk input i and piece g < GPT = 64 / S, workgroup w = (tbl np
-// + i) GPT + g's [plane][channel][S-byte piece] (piece g = spectra g T ..
-// g T + T - 1 of the block).  A thread takes one 16-byte quarter v of the 64-byte
-// rows (k, tb, p, plane) of PV neighbouring channels: PV loads of 16 bytes, one
-// from each piece, and PV stores.  Of a wave's lanes, those of the four quarters
-// and two planes write a whole 128-byte line, and those of eight channel groups
-// read one.  Bound: HBM.  (One channel per thread, so 16 / S loads of S bytes for
-// each store: 2048 channels int8, 8.6 GB, 1.96 ms, now 1.71 = 5.0 TB/s, the copy
-// rate; 4096 channels FP8 1.20 -> 0.89; 8192 FP16 0.24 -> 0.15.)
-template <int S>
+// block tbl, chunk input i and piece g < GPT = TB / T, workgroup w = (tbl np + i)
+// GPT + g's pairs, [channel][spectrum][part] (piece g = spectra g T .. g T + T - 1
+// of the block).  A thread takes one 16-byte quarter v of both planes' 64-byte
+// rows (k, tb, p) of KG neighbouring channels: 16-byte loads from each of its
+// pieces, the pairs parted and put in order in registers, 16-byte stores.  Of a
+// wave's lanes those of the four quarters write whole rows, and those of 16
+// channel groups read 256 bytes together.  Bound: HBM.  (One channel per thread,
+// so up to 16 loads of 1 to 8 bytes for each store: 2048 channels int8, 8.6 GB,
+// 1.96 ms, now 1.66 = 5.2 TB/s, the copy rate; 4096 FP8 1.20 -> 0.92; 8192 FP16
+// 0.24 -> 0.16.)
+template <int ES, int T>
 __global__ __launch_bounds__(256) void fgather_kernel(const uint8_t *__restrict__ scr, uint8_t *__restrict__ spec,
                                                       int log2c, int np, int64_t total, int64_t ks, int64_t ts,
                                                       int tb_first, int p0) {
-    static_assert(S == 1 || S == 2 || S == 4 || S == 8 || S == 16, "piece size");
-    constexpr int GPT = kRowBytes / S, PV = 16 / S;
+    constexpr int PB = 2 * ES * T;                     // bytes of a piece of one channel
+    constexpr int TB = kRowBytes / ES, GPT = TB / T, VE = 16 / ES;   // elements of a row, pieces, of a quarter
+    constexpr int NP = VE / T > 0 ? VE / T : 1;        // pieces of a quarter
+    constexpr int KG = PB < 16 ? 16 / PB : 1;          // channels
+    constexpr int L = PB > 16 ? PB / 16 : 1;           // loads per piece
+    static_assert(NP * T == VE, "a quarter is whole pieces");
     const int C = 1 << log2c;
-    const int64_t wg_bytes = (int64_t)2 * C * S;
+    const int64_t wg_bytes = (int64_t)C * PB;
     const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (e >= total) return;
-    const int v = (int)(e & 3), pl = (int)(e >> 2) & 1;
-    const int64_t r = e >> 3;
-    const int k0 = (int)(r & (C / PV - 1)) * PV;
-    const int64_t r2 = r / (C / PV);
+    const int v = (int)(e & 3);
+    const int64_t r = e >> 2;
+    const int k0 = (int)(r & (C / KG - 1)) * KG;
+    const int64_t r2 = r / (C / KG);
     const int i = (int)(r2 % np), tbl = (int)(r2 / np);
-    const uint8_t *src = scr + ((int64_t)(tbl * np + i) * GPT + v * PV) * wg_bytes + (int64_t)(pl * C + k0) * S;
+    const uint8_t *src = scr + ((int64_t)(tbl * np + i) * GPT + v * NP) * wg_bytes + (int64_t)k0 * PB;
     uint8_t *dst = spec + (int64_t)(tb_first + tbl) * ts + (int64_t)k0 * ks + (int64_t)(p0 + i) * (2 * kRowBytes) +
-                   pl * kRowBytes + v * 16;
-    uint4 in[PV], out[PV];
+                   v * 16;
+    uint4 in[NP * L];
 #pragma unroll
-    for (int u = 0; u < PV; ++u) in[u] = *reinterpret_cast<const uint4 *>(src + u * wg_bytes);
-    transpose_pieces<S>(in, out);
+    for (int u = 0; u < NP * L; ++u)
+        in[u] = *reinterpret_cast<const uint4 *>(src + u / L * wg_bytes + u % L * 16);
+    uint32_t a[NP * L * 4];
+    __builtin_memcpy(a, in, sizeof a);
+    const auto word = [&](int x) { return a[x]; };
 #pragma unroll
-    for (int j = 0; j < PV; ++j) *reinterpret_cast<uint4 *>(dst + j * ks) = out[j];
+    for (int g = 0; g < KG; ++g)
+#pragma unroll
+        for (int pl = 0; pl < 2; ++pl) {
+            // element s of the quarter: pair (g, s mod T) of piece s / T
+            const auto pos = [&](int s) { return s / T * (16 * L / (2 * ES)) + g * T + s % T; };
+            uint4 out;
+            out.x = plane_word<ES>(word, pos, pl, 0);
+            out.y = plane_word<ES>(word, pos, pl, 1);
+            out.z = plane_word<ES>(word, pos, pl, 2);
+            out.w = plane_word<ES>(word, pos, pl, 3);
+            *reinterpret_cast<uint4 *>(dst + g * ks + pl * kRowBytes) = out;
+        }
 }
 
 template <int PREC, int C, bool REAL>
@@ -768,7 +800,7 @@ hipError_t launch_c(int N, const void *in, int64_t ld, int n_spectra, const floa
     } else {
         // Chunks of whole time blocks of all inputs, or of one time block of
         // a range of inputs, each filling at most the scratch.
-        constexpr int S = T * (int)sizeof(typename Elem<PREC>::T);
+        constexpr int ES = Pair<PREC>::ES, KG = 2 * ES * T < 16 ? 16 / (2 * ES * T) : 1;
         const int64_t unit = (int64_t)C * 2 * kRowBytes;
         if (!scr.buf || scr.bytes < unit) return hipErrorInvalidValue;
         const int np = (int)std::min<int64_t>(N, scr.bytes / unit);
@@ -788,8 +820,8 @@ hipError_t launch_c(int N, const void *in, int64_t ld, int n_spectra, const floa
                                                                    (int64_t)s0 * C);
                 hipError_t e = run(src, npc, ns, sb, 0, tbc == 0 && p0 == 0 ? scale2 : nullptr);
                 if (e != hipSuccess) return e;
-                const int64_t total = (int64_t)ntb_c * npc * 2 * C * 4 / (16 / S);
-                hipLaunchKernelGGL(fgather_kernel<S>, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, stream, sb,
+                const int64_t total = (int64_t)ntb_c * npc * 4 * (C / KG);
+                hipLaunchKernelGGL((fgather_kernel<ES, T>), dim3((unsigned)((total + 255) / 256)), dim3(256), 0, stream, sb,
                                    static_cast<uint8_t *>(spec), log2c, npc, total, lay.ks, lay.ts, tb0 + tbc, p0);
                 if ((e = hipGetLastError()) != hipSuccess) return e;
             }
