@@ -38,6 +38,8 @@
 namespace corr {
 namespace {
 
+constexpr int kMaxC = 8192;                       // channels, at most
+
 // The complex FP32 form at 2048 and 4096 channels stores straight into the
 // held rows (in 16-byte pieces of each) instead of through the chunked gather:
 // 2048 channels from 256-thread workgroups, two per CU (1024 inputs x 512
@@ -223,12 +225,28 @@ template <int C, int T, int TH, int R, int NS> struct WriteAt {
 
 // First Stockham pass, radix R: butterfly (t, j) takes x[t][j + r C/R] straight
 // from global memory (spectra past n_spectra read as zero) and does an R-point
-// DFT; no twiddles precede the first pass.  The loads are unconditional (a
-// padding spectrum reads spectrum 0, which always exists, and is then zeroed)
-// so that all of a thread's loads are in flight together: a load under a
-// branch whose value is converted inside it would be waited for one by one.
-__device__ __forceinline__ float2 to_f2(float2 x) { return x; }
-__device__ __forceinline__ float2 to_f2(char2 x) { return make_float2((float)x.x, (float)x.y); }
+// DFT; no twiddles precede the first pass.  The loads are unconditional so that
+// all of a thread's loads are in flight together: a load under a branch whose
+// value is converted inside it would be waited for one by one.  A padding
+// spectrum reads a row of zeros with radix 8: one choice of address in place of
+// one for each value (128 channels real-input int8 0.235 -> 0.227 ms, 8192 FP32
+// 0.98 -> 0.89).  With radices 16 and 32 it reads spectrum 0 (which always
+// exists) and zeroes what it read: without the choice between them and the
+// first sums (or the conversions in its sight) the compiler joins other
+// multiplications and additions there, and the spectra round otherwise.
+__device__ float2 zero_row[kMaxC];                // (device globals start as zeros; never written)
+template <bool> __device__ __forceinline__ float2 to_f2(float2 x) { return x; }
+// Two signed bytes.  SIGNED: by conversions that take a byte with its sign as it
+// is (the compiler extends each first).
+template <bool SIGNED> __device__ __forceinline__ float2 to_f2(char2 x) {
+    if constexpr (!SIGNED) return make_float2((float)x.x, (float)x.y);
+    uint16_t u;
+    __builtin_memcpy(&u, &x, 2);
+    float2 f;
+    asm("v_cvt_f32_i32_sdwa %0, sext(%1) dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:BYTE_0" : "=v"(f.x) : "v"((uint32_t)u));
+    asm("v_cvt_f32_i32_sdwa %0, sext(%1) dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:BYTE_1" : "=v"(f.y) : "v"((uint32_t)u));
+    return f;
+}
 
 // Plain or non-temporal (streaming) load of one input element.
 template <bool NT>
@@ -256,15 +274,16 @@ __device__ __forceinline__ void first_pass(float2 *v, const Src *__restrict__ sr
         int t, j;
         bfly_index<C, T, TH, R, MAP_PLAIN>(tid, q, t, j);
         float2 *x = v + q * R;
-        const bool ok = (a0 + t) < n_spectra;
-        const Src *row = src + (int64_t)(ok ? a0 + t : 0) * C + j;
+        constexpr bool ZEROS = R <= 8;
+        const bool ok = a0 + t < n_spectra;
+        const Src *row = (ok || !ZEROS ? src + (int64_t)(ok ? a0 + t : 0) * C : reinterpret_cast<const Src *>(zero_row)) + j;
         Src raw[R];
 #pragma unroll
         for (int r = 0; r < R; ++r) raw[r] = ld_in<NT>(row + r * CR);
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-            const float2 f = to_f2(raw[r]);
-            x[r] = make_float2(ok ? f.x : 0.f, ok ? f.y : 0.f);
+            const float2 f = to_f2<ZEROS>(raw[r]);
+            x[r] = make_float2(ok || ZEROS ? f.x : 0.f, ok || ZEROS ? f.y : 0.f);
         }
         Dft<R>::run(x);
     }
