@@ -165,11 +165,10 @@ bool aligned(const void *ptr, size_t a) { return ((uintptr_t)ptr % a) == 0; }
 // the time: a 64-input block ends sooner (256 inputs x 128 channels FP32, 384
 // blocks of 128: 55 / 67 us; x 512, 1536 blocks: 218 / 205 us; 512 inputs x 256
 // channels int8, 2560: 131 / 146 us; x 512, 5120: 334 / 287 us).  Against the
-// better of both at 137 shapes of 65..1024 inputs x 16..2048 channels the rule
-// loses 0.2% (FP32, FP8, int8) to 0.6% (FP16) on average.
-int default_tile(int prec, int64_t n64, int64_t n128, int C) {
-    return 5 * n64 >= 16 * n128 && C * n128 >= (prec == P_FP32 ? 1280 : 4096) ? 128 : 64;
-}
+// better of both at 137 shapes of 65..1024 inputs x 16..2048 channels, each of 3,
+// 12 and 40 time blocks, the rule loses 0.2% to 1.3% on average, depending on
+// form and length.
+int default_tile(int64_t n64, int64_t n128, int C) { return 5 * n64 >= 16 * n128 && C * n128 >= 2000 ? 128 : 64; }
 
 int64_t tri_blocks(int N, int tile) {
     const int64_t n = (N + tile - 1) / tile;
@@ -177,15 +176,15 @@ int64_t tri_blocks(int N, int tile) {
 }
 
 // For the triangle of N inputs.
-int default_tile(int prec, int N, int C) { return default_tile(prec, tri_blocks(N, 64), tri_blocks(N, 128), C); }
+int default_tile(int N, int C) { return default_tile(tri_blocks(N, 64), tri_blocks(N, 128), C); }
 
-int effective_tile(const corr_ctx *h) { return h->tile ? h->tile : default_tile(h->prec, h->N, h->C); }
+int effective_tile(const corr_ctx *h) { return h->tile ? h->tile : default_tile(h->N, h->C); }
 
 // For ni rows against nj columns.
 int rect_tile(const corr_ctx *h, int ni, int nj) {
     if (h->tile) return h->tile;
     auto blocks = [&](int64_t t) { return ((ni + t - 1) / t) * ((nj + t - 1) / t); };
-    return default_tile(h->prec, blocks(64), blocks(128), h->C);
+    return default_tile(blocks(64), blocks(128), h->C);
 }
 
 const float *x_scale(const corr_ctx *h) {
@@ -808,7 +807,7 @@ corr_status corr_autotune(corr_handle h, int32_t n_spectra, int32_t *tile_out) {
     }
     const int Ct = tune_channels(h);
     const int cand[2] = {64, 128};
-    const int def_tile = default_tile(h->prec, h->N, h->C);
+    const int def_tile = default_tile(h->N, h->C);
     float best_ms = 0, def_ms = 0;
     int best = 0;
     {
@@ -883,7 +882,7 @@ corr_status corr_autotune_fx(corr_handle h, const void *d_volts, int64_t ld_samp
 
     const int n_tb = (n_spectra + h->TB - 1) / h->TB;
     const bool def_tb = default_tb_major(h->C, h->N, elem_bytes(h->prec));
-    const int def_tile = default_tile(h->prec, h->N, h->C);
+    const int def_tile = default_tile(h->N, h->C);
     const TuneKey key{h->arch, 1, h->prec, (h->N + 63) / 64, h->C, n_tb, 0};
     TuneVal best{def_tile, def_tb ? 1 : 0};
     float best_ms = 0, def_ms = 0;
@@ -1292,7 +1291,7 @@ corr_status corr_xengine_noalloc(const corr_params *params, const void *d_spectr
                                    UserScale{d_inv_scale, scaled && k0 == 0 ? s2 : nullptr, C}, stream);
         if (e != hipSuccess) return hip_fail(nullptr, e, "ingest launch");
         uint8_t *vis = static_cast<uint8_t *>(d_vis) + (int64_t)k0 * B * 8;
-        e = launch_xengine(prec, default_tile(prec, N, n), n, N, n_spectra, spec, lay, scaled ? s2 + k0 : nullptr, vis, vis,
+        e = launch_xengine(prec, default_tile(N, n), n, N, n_spectra, spec, lay, scaled ? s2 + k0 : nullptr, vis, vis,
                            accumulate ? 0 : 1, stream);
         if (e != hipSuccess) return hip_fail(nullptr, e, "xengine launch");
     }

@@ -563,71 +563,120 @@ __device__ __forceinline__ void tile(uint8_t *smem, const uint8_t *__restrict__ 
     } else {
         sum(std::false_type{});
     }
-    if (!active) return;
-    // Epilogue: element r of a 32x32 block is (row 8(r/4) + 4h + r%4, column m).
-    // Rows go in batches of EH; each batch's accumulator reads are issued
-    // before any of its writes.  The writes are streaming (non-temporal) so
-    // that they displace fewer of the spectra rows other blocks still read
-    // from L2 (FP8, 1024 inputs x 4096 channels: 9.45 -> 9.1-9.3 ms).  Elements outside the triangle (rectangle) or
-    // past N read a valid address and are not written.  Offsets within a
-    // channel fit 32 bits (N(N+1)/2 and N^2 < 2^31 for N <= 8192).
+    // Epilogue.  Element r of a 32x32 block is (row 8(r/4) + 4h + r%4, column m).
+    // The writes are streaming (non-temporal) so that they displace fewer of the
+    // spectra rows other blocks still read from L2 (FP8, 1024 inputs x 4096
+    // channels: 9.45 -> 9.1-9.3 ms).  Pairs outside the triangle (rectangle) or
+    // past N read a valid place and are not written.  Offsets within a channel
+    // fit 32 bits (N(N+1)/2 and N^2 < 2^31 for N <= 8192).
     using E = typename std::conditional<PREC == P_INT8, int, float>::type;
     typedef E T2 __attribute__((ext_vector_type(2)));
     typedef __attribute__((address_space(1))) T2 gT2;
     gT2 *out = (gT2 *)acc_out + (int64_t)k * B;
     const gT2 *in = (const gT2 *)acc_in + (int64_t)k * B;   // the sums so far (== out except when dumping)
     const float s2 = (PREC != P_INT8 && scale2) ? ((gf32 *)scale2)[k] : 1.0f;
-    // rows of a block per batch of accumulator reads: all 16 where a wave has
-    // one row block, 8 where it has two (the registers allow no more)
-    constexpr int EH = FR == 1 ? 16 : 8;
+    if constexpr (TILE == 128) {
+        // 128-input blocks: row block f of every wave is laid out in LDS as 64 rows
+        // of TILE pairs, and the workgroup writes it from there row by row: a row's
+        // places are computed once, and its 1 KB goes out as one run of 16-byte
+        // stores.  Straight from the registers, as below, each pair had its place
+        // computed and rows went out in runs of 256 bytes: 512 inputs x 2048
+        // channels x 128 FP8 spectra 0.76 -> 0.56 ms, 1024 x 1024 x 256 1.35 -> 1.1-1.2,
+        // 512 x 2048 x 32 FP32 0.99 -> 0.73; nothing where the sums take long.
+        typedef E T4 __attribute__((ext_vector_type(4)));
+        typedef T4 T4u __attribute__((aligned(8)));
+        typedef __attribute__((address_space(1))) T4u gT4;
+        static_assert(64 * TILE * sizeof(T2) <= ring_bytes(TILE) && TILE / QS == 2, "a row block of all waves fits the ring");
+        T2 *const rows = reinterpret_cast<T2 *>(smem);
+        constexpr int R = 64 / NW;                         // rows per wave
+        const int j = J0 + 2 * lane;                       // the lane's two columns are j and j + 1
 #pragma unroll
-    for (int f = 0; f < FR; ++f)
+        for (int f = 0; f < FR; ++f) {
+            __syncthreads();                               // the ring, or the last row block, has been read
+            if (active && !(dwave && skipped<FR, 1>(f)) && !(lwave && skipped<FR, 2>(f))) {
+                T2 *w = rows + (wi * 32 + 4 * h) * TILE + wj * QC + m;
 #pragma unroll
-    for (int c = 0; c < FC; ++c) {
-        if ((dwave && skipped<FR, 1>(f)) || (lwave && skipped<FR, 2>(f))) continue;
-        const int j = J0 + wj * QC + 32 * c + m;
+                for (int c = 0; c < FC; ++c)
 #pragma unroll
-        for (int hh = 0; hh < 16 / EH; ++hh) {
-            int idx[EH];
-            uint32_t ok = 0;
-#pragma unroll
-            for (int q = 0; q < EH; ++q) {
-                const int r = EH * hh + q;
-                const int i = I0 + wi * QS + f * 32 + 8 * (r >> 2) + 4 * h + (r & 3);
-                bool inside;
-                int o;
-                if constexpr (RECT) {
-                    inside = i < om.r_end && j < om.c_end;
-                    o = (i - om.r0) * (om.c_end - om.c0) + (j - om.c0);
-                } else {
-                    inside = i < N && j <= i;
-                    o = i * (i + 1) / 2 + j;
-                }
-                ok |= (uint32_t)inside << q;
-                idx[q] = inside ? o : 0;
+                    for (int r = 0; r < 16; ++r)
+                        w[(8 * (r >> 2) + (r & 3)) * TILE + 32 * c] = T2{re[f][c][r], im[f][c][r]};
             }
-            T2 old[EH];
+            __syncthreads();
+            int o[R];
+            bool one[R], two[R];                           // whether the lane's first and second pair are written
+            T2 old[R][2];
+#pragma unroll
+            for (int q = 0; q < R; ++q) {
+                const int lr = wave * R + q;
+                const int i = I0 + (lr >> 5) * QS + f * 32 + (lr & 31);
+                if constexpr (RECT) {
+                    one[q] = i < om.r_end && j < om.c_end;
+                    two[q] = i < om.r_end && j + 1 < om.c_end;
+                    o[q] = (i - om.r0) * (om.c_end - om.c0) + (j - om.c0);
+                } else {
+                    one[q] = i < N && j <= i;
+                    two[q] = i < N && j + 1 <= i;
+                    o[q] = i * (i + 1) / 2 + j;
+                }
+            }
             if (!first_call) {
 #pragma unroll
-                for (int q = 0; q < EH; ++q) old[q] = in[idx[q]];
+                for (int q = 0; q < R; ++q) {
+                    old[q][0] = in[one[q] ? o[q] : 0];
+                    old[q][1] = in[two[q] ? o[q] + 1 : 0];
+                }
             }
 #pragma unroll
-            for (int q = 0; q < EH; ++q) {
-                const int r = EH * hh + q;
-                const int i = I0 + wi * QS + f * 32 + 8 * (r >> 2) + 4 * h + (r & 3);
-                T2 v;
-                const bool auto_ = !RECT && i == j;
-                if constexpr (PREC == P_INT8) {
-                    v = T2{re[f][c][r], auto_ ? 0 : im[f][c][r]};
-                } else {
-                    v = T2{re[f][c][r] * s2, auto_ ? 0.0f : im[f][c][r] * s2};
-                }
-                if (!first_call) {
-                    v.x += old[q].x;
-                    v.y += old[q].y;
-                }
-                if ((ok >> q) & 1u) __builtin_nontemporal_store(v, &out[idx[q]]);
+            for (int q = 0; q < R; ++q) {
+                const int lr = wave * R + q;
+                const int i = I0 + (lr >> 5) * QS + f * 32 + (lr & 31);
+                T4 v = *reinterpret_cast<const T4 *>(rows + lr * TILE + 2 * lane);
+                if constexpr (PREC != P_INT8) v *= s2;
+                if (!RECT && i == j) v[1] = 0;             // autos
+                if (!RECT && i == j + 1) v[3] = 0;
+                if (!first_call) v += T4{old[q][0].x, old[q][0].y, old[q][1].x, old[q][1].y};
+                if (two[q]) __builtin_nontemporal_store(v, (gT4 *)&out[o[q]]);
+                else if (one[q]) __builtin_nontemporal_store(T2{v[0], v[1]}, &out[o[q]]);
             }
+        }
+    } else {
+        // 64-input blocks, one 32x32 block a wave: from the registers (rows of
+        // 512 bytes through LDS gained nothing: 200 inputs x 8192 channels x 128
+        // FP8 spectra 0.43 -> 0.46-0.50 ms, 100 x 2048 x 500 FP16 0.125 -> 0.129).
+        // All accumulator reads are issued before any of the writes.
+        static_assert(FR * FC == 1, "one block a wave");
+        if (!active) return;
+        const int j = J0 + wj * QC + m;
+        int idx[16];
+        uint32_t ok = 0;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const int i = I0 + wi * QS + 8 * (r >> 2) + 4 * h + (r & 3);
+            bool inside;
+            int o;
+            if constexpr (RECT) {
+                inside = i < om.r_end && j < om.c_end;
+                o = (i - om.r0) * (om.c_end - om.c0) + (j - om.c0);
+            } else {
+                inside = i < N && j <= i;
+                o = i * (i + 1) / 2 + j;
+            }
+            ok |= (uint32_t)inside << r;
+            idx[r] = inside ? o : 0;
+        }
+        T2 old[16];
+        if (!first_call) {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) old[r] = in[idx[r]];
+        }
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const int i = I0 + wi * QS + 8 * (r >> 2) + 4 * h + (r & 3);
+            T2 v{re[0][0][r], im[0][0][r]};
+            if constexpr (PREC != P_INT8) v *= s2;
+            if (!RECT && i == j) v.y = 0;              // autos
+            if (!first_call) v += old[r];
+            if ((ok >> r) & 1u) __builtin_nontemporal_store(v, &out[idx[r]]);
         }
     }
 }
