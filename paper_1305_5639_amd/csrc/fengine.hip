@@ -1,7 +1,7 @@
 // F-engine: channelising FFT (Section 2, Eq. 1) with a fused requantise
 // epilogue that writes the X-engine's time-blocked planar spectra layout.
 //
-// One workgroup of TH threads (256, or 512 for some int8 / FP8 sizes)
+// One workgroup of TH threads (256, or 512 for some sizes)
 // transforms T = TH PT / C consecutive spectra of
 // one input (64 KB of complex64 voltages, one contiguous coalesced run); every
 // thread holds PT = 32 complex values.  The FFT is a Stockham autosort transform
@@ -12,9 +12,9 @@
 // strided Stockham stores and loads are free of bank conflicts.  The last pass
 // maps neighbouring lanes to neighbouring spectra of one channel; its values
 // are scaled by inv_s[k], rounded to the spectra element type and staged in
-// LDS as [plane][channel][spectrum], which turns the channel-major FFT output
-// into runs of consecutive spectra per (channel, input, plane) row of the
-// X-engine layout.  From kGatherMinC channels on, a workgroup's staged output
+// LDS as [channel][spectrum][part], which turns the channel-major FFT output
+// into runs of consecutive spectra per channel, parted into the (channel,
+// input, plane) rows of the X-engine layout as they are stored.  From kGatherMinC channels on, a workgroup's staged output
 // goes instead to a scratch buffer in workgroup order, and fgather_kernel
 // assembles the rows from those pieces.
 //
@@ -53,15 +53,17 @@ constexpr bool fp32_direct() {
     return !REAL && PREC == P_FP32 && (C == 2048 || C == 4096);
 }
 
-// Threads per workgroup: 256, or 512 for the int8 / FP8 complex forms at C =
+// Threads per workgroup: 256, or 512 for the low-precision complex forms at C =
 // 512 and 1024, where twice the spectra per workgroup (so half as many
-// partial output rows) measured 3-10% faster on 2^28 samples; at 256 channels
+// partial output rows) measured 3-10% faster on 2^28 samples for int8 and FP8
+// and more for FP16 (512 inputs x 512 channels x 512 spectra 0.41 -> 0.33 ms,
+// 256 x 1024 x 64 0.062 -> 0.043); at 256 channels
 // they gained nothing; and for fp32_direct as said there.  From 2048 channels the
 // chunked store and gather leave no partial rows to save.
 template <int C, int PREC, bool REAL>
 constexpr int threads() {
     if (fp32_direct<C, PREC, REAL>()) return C == 2048 ? 256 : 512;
-    return (!REAL && (PREC == P_INT8 || PREC == P_FP8) && (C == 512 || C == 1024)) ? 512 : 256;
+    return (!REAL && PREC != P_FP32 && (C == 512 || C == 1024)) ? 512 : 256;
 }
 
 // Complex values per thread.  64 once paid at C >= 4096, where 32 left a
@@ -248,11 +250,15 @@ template <bool SIGNED> __device__ __forceinline__ float2 to_f2(char2 x) {
     return f;
 }
 
-// Plain or non-temporal (streaming) load of one input element.
-template <bool NT>
+// Load of one input element: plain, or as one 64-bit word, plain or non-temporal
+// (streaming).  The word forms round alike; the compiler's choice of fused
+// multiply-adds after a plain load is another at 16 and 32 channels.
+enum Load { LOAD_PLAIN, LOAD_WORD, LOAD_STREAM };
+template <int LD>
 __device__ __forceinline__ float2 ld_in(const float2 *p) {
-    if constexpr (NT) {
-        const unsigned long long u = __builtin_nontemporal_load(reinterpret_cast<const unsigned long long *>(p));
+    if constexpr (LD != LOAD_PLAIN) {
+        const unsigned long long *q = reinterpret_cast<const unsigned long long *>(p);
+        const unsigned long long u = LD == LOAD_STREAM ? __builtin_nontemporal_load(q) : *q;
         float2 r;
         __builtin_memcpy(&r, &u, sizeof r);
         return r;
@@ -260,12 +266,12 @@ __device__ __forceinline__ float2 ld_in(const float2 *p) {
         return *p;
     }
 }
-template <bool NT>
+template <int LD>
 __device__ __forceinline__ char2 ld_in(const char2 *p) {
     return *p;
 }
 
-template <int C, int T, int TH, int R, bool NT, typename Src>
+template <int C, int T, int TH, int R, int LD, typename Src>
 __device__ __forceinline__ void first_pass(float2 *v, const Src *__restrict__ src, int a0, int n_spectra,
                                            int tid) {
     constexpr int Q = T * C / TH / R, CR = C / R;
@@ -279,7 +285,7 @@ __device__ __forceinline__ void first_pass(float2 *v, const Src *__restrict__ sr
         const Src *row = (ok || !ZEROS ? src + (int64_t)(ok ? a0 + t : 0) * C : reinterpret_cast<const Src *>(zero_row)) + j;
         Src raw[R];
 #pragma unroll
-        for (int r = 0; r < R; ++r) raw[r] = ld_in<NT>(row + r * CR);
+        for (int r = 0; r < R; ++r) raw[r] = ld_in<LD>(row + r * CR);
 #pragma unroll
         for (int r = 0; r < R; ++r) {
             const float2 f = to_f2<ZEROS>(raw[r]);
@@ -408,11 +414,11 @@ template <int C, int PT = 32> struct Last {
 
 // The passes of Plan<C>; v ends with the last pass's outputs in registers,
 // laid out by mapping LMAP.
-template <int C, int T, int TH, bool SPLIT, int LMAP, bool NT, typename Src>
+template <int C, int T, int TH, bool SPLIT, int LMAP, int LD, typename Src>
 __device__ __forceinline__ void fft(float2 *v, float *lds, const Src *__restrict__ src, int a0, int n_spectra,
                                     const float2 *__restrict__ tw, int tid) {
     using P = Plan<C>;
-    first_pass<C, T, TH, P::R0, NT>(v, src, a0, n_spectra, tid);
+    first_pass<C, T, TH, P::R0, LD>(v, src, a0, n_spectra, tid);
     if constexpr (P::NP == 2) {
         exchange<C, T, TH, P::R0, 1, P::R1, LMAP, SPLIT>(v, lds, tid, false);
         later_pass<C, T, TH, P::R1, P::R0, LMAP>(v, tw, tid);
@@ -635,21 +641,13 @@ __global__ __launch_bounds__((threads<C, PREC, REAL>())) __attribute__((amdgpu_w
     // workgroups per CU, one round per reordering), and so does the
     // real-input form where the partners of its split step come through LDS.
     constexpr bool SPLIT = PREC != P_FP32 && !(REAL && Last<C>::REAL_VIA_LDS);
-    // Two code-shape choices, both measured (MWA-like 256 x 1024 x 1000 and
-    // 2048 streams x 256-point real transforms):
-    //  - NT: the int8 / FP8 complex forms read the voltages with streaming
-    //    (non-temporal) loads, 0.73 -> 0.64 ms; FP32 / FP16 and the
-    //    real-input forms gain nothing or lose.
-    //  - SCALE_TEST: the FP32 / FP16 complex forms keep a null test on the
-    //    scale table (the host never passes null).  The compiler then loads
-    //    the scales one pair at a time inside the staging loop, and the
-    //    kernel's half-written spectra lines merge far better in L2: FP32
-    //    writes 2.47 GB instead of 3.10 GB and takes 1.16 instead of
-    //    1.53 ms (FP16 0.79 instead of 1.06 ms).  An explicit wait after each
-    //    scale load recovers only part of that, and the other forms are
-    //    faster without the test.
-    constexpr bool NT = !REAL && (PREC == P_INT8 || PREC == P_FP8);
-    constexpr bool SCALE_TEST = !REAL && (PREC == P_FP32 || PREC == P_FP16);
+    // LD: int8 and FP8 read the voltages with streaming (non-temporal) loads from
+    // 256 channels on (512 inputs x 256 channels x 1024 spectra int8 0.28 ms,
+    // without 0.32; 512 x 512 x 512 0.31, 0.34; 512 x 1024 x 512 0.72, 0.77; above that
+    // within 2%).  Below, a wave's loads of one spectrum are a few lines or part
+    // of one, gone before the next load of the rest (1024 x 32 x 8192 1.14 ms,
+    // without 0.54; 1024 x 64 x 4096 0.58, 0.54).  FP32 and FP16 gain nothing or lose.
+    constexpr int LD = REAL || PREC == P_FP32 || PREC == P_FP16 ? LOAD_PLAIN : C >= 256 ? LOAD_STREAM : LOAD_WORD;
     // GATHER: stores go to the chunk scratch (passed as spec) in natural
     // order, [workgroup][plane][channel][spectrum], contiguous per workgroup.
     constexpr bool GATHER = C >= kGatherMinC && !fp32_direct<C, PREC, REAL>();
@@ -680,11 +678,11 @@ __global__ __launch_bounds__((threads<C, PREC, REAL>())) __attribute__((amdgpu_w
     float2 v[PT];
     if constexpr (REAL) {
         const char2 *src = reinterpret_cast<const char2 *>(static_cast<const int8_t *>(in) + (int64_t)p * ld);
-        fft<C, T, TH, SPLIT, LMAP, false>(v, lds, src, a0, n_spectra, tw, tid);
+        fft<C, T, TH, SPLIT, LMAP, LOAD_PLAIN>(v, lds, src, a0, n_spectra, tw, tid);
         if constexpr (Last<C>::REAL_VIA_LDS) real_split_lds<C, T, TH, RL, SPLIT>(v, lds, tw2, tid);
         else real_split_regs<C, T, TH, RL>(v, tw2, tid);
     } else {
-        fft<C, T, TH, SPLIT, LMAP, NT>(v, lds, static_cast<const float2 *>(in) + (int64_t)p * ld, a0, n_spectra, tw,
+        fft<C, T, TH, SPLIT, LMAP, LD>(v, lds, static_cast<const float2 *>(in) + (int64_t)p * ld, a0, n_spectra, tw,
                                    tid);
     }
 
@@ -707,7 +705,7 @@ __global__ __launch_bounds__((threads<C, PREC, REAL>())) __attribute__((amdgpu_w
 #pragma unroll
         for (int r = 0; r < RL; ++r) {
             const int k = j + r * CR;
-            const float sc = SCALE_TEST ? (inv_scale ? inv_scale[k] : 1.0f) : inv_scale[k];
+            const float sc = inv_scale[k];
             const float2 y = v[q * RL + r];
             *reinterpret_cast<PT2 *>(stage + (k * T + t) * (2 * ES)) = PR::conv(y.x * sc, y.y * sc);
         }
