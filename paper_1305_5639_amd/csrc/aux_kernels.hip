@@ -1,6 +1,6 @@
 // Data-movement kernels around the two engines: caller spectra in and out of
-// the time-blocked planar layout, dump layout/order conversion and a zero fill.  None of these is on the F -> X hot path; the
-// spectra moves are LDS-tiled transposes, the rest coalesced element maps.
+// the time-blocked planar layout, dump layout/order conversion and a zero fill.
+// The spectra moves and the dump conversions are tiled transposes through LDS.
 #include "corr_internal.h"
 
 namespace corr {
@@ -9,24 +9,24 @@ namespace {
 constexpr int kThreads = 256;
 
 
-// Caller spectra <-> held rows.  For channel k and time block tb, the TB
-// public rows a = tb*TB + t hold the 2N columns (2p + plane) of that channel
-// contiguously; the held layout wants each column's TB values contiguous (one
-// 64-byte plane row).  That is a TB x 2N transpose per (k, tb).  One
-// workgroup moves a tile of kCols columns: TB public segments of kCols * ES
-// bytes <-> kCols held rows of 64 bytes, 16 KB either way, through LDS.  Both
-// sides move 16-byte vectors; the LDS row of public row t stores its 16-byte
-// chunks XOR-swizzled by the held vector t falls in, so the gathers of one
-// wave (16 columns x 4 held vectors) hit distinct banks.
+// Caller spectra <-> held rows.  The public row of a spectrum holds C x 2N
+// columns (k, 2p + plane) one after the other; the held layout wants each
+// column's TB values of a time block contiguous (one 64-byte plane row).  That is
+// a TB x C 2N transpose per time block, in tiles of kCols columns whatever their
+// channels (a tile of one channel's columns would be part empty: 48 inputs have
+// 96): TB public segments of kCols * ES bytes <-> kCols held rows of 64 bytes.  A
+// thread moves 4 16-byte vectors either way, the public ones from 4 / ES
+// neighbouring spectra, which it transposes in registers into dwords of 4 / ES
+// spectra of one column; LDS holds a tile's dwords as [16 bytes of columns]
+// [column][dword] with 4 dwords of padding, so that a wave's 16 vectors x 4 dwords
+// hit distinct banks on the public side, and the held side reads whole vectors.
+// Bound: HBM, and for small calls the latency of one load and one store.
+// (Per-channel tiles with a scalar path where 2N ES is no multiple of 16, loads
+// under branches and a byte or half at a time out of LDS, against now, ingest and
+// export: 48 inputs x 256 channels x 512 int8 12.2 -> 9.4 us, 7.1 -> 6.7; 300 x 256 x
+// 1000 int8 198 -> 49, 251 -> 55; 300 x 1024 x 1000 FP16 465 -> 449, 686 -> 486 = 5.1
+// TB/s, the copy rate; 1 input x 1024 x 4096 int8 with its X pass 182 -> 22.)
 constexpr int kCols = 256;
-
-template <typename T>
-__device__ __forceinline__ int lds_elem(int t, int j) {
-    constexpr int ES = (int)sizeof(T), VE = 16 / ES, W = kCols * ES;
-    const int byte = j * ES, chunk = byte >> 4;
-    const int tg = (t / VE) & 3;
-    return t * W + ((chunk ^ (tg * ES)) << 4) + (byte & 15);
-}
 
 // Byte-wise max(b, -127) of four int8 values: a byte equal to 0x80 (-128)
 // becomes 0x81 (-127), every other byte is unchanged.  x marks the -128 bytes
@@ -37,88 +37,148 @@ __device__ __forceinline__ uint32_t sat_int8x4(uint32_t v) {
     return v | ((~nz & 0x80808080u) >> 7);
 }
 
-// INGEST: public src -> held dst (the tail of the last block zero-filled);
-// else held src -> public dst.  VEC: public rows 16-byte aligned (2N * ES a
-// multiple of 16, base aligned), so public segments move as vectors.  SAT8
-// (int8 ingest): -128 is read as -127, the symmetric range the X-engine's
-// exact negation and the int32 overflow bound assume.
-template <typename T, bool INGEST, bool VEC, bool SAT8 = false>
-__global__ __launch_bounds__(kThreads) void relayout_kernel(const uint8_t *__restrict__ src,
-                                                             uint8_t *__restrict__ dst, int C, int N,
-                                                             int n_spectra, int n_tb, int n_cc, SpecLayout lay,
-                                                             UserScale us) {
-    constexpr int ES = (int)sizeof(T), TB = kRowBytes / ES, VE = 16 / ES, W = kCols * ES;
-    constexpr int PUB_VECS = TB * (W / 16);             // 1024 either side
-    __shared__ __align__(16) uint8_t lds[TB * W];
-    const int64_t g = blockIdx.x;
-    const int cc = (int)(g % n_cc);
-    const int tb = (int)((g / n_cc) % n_tb);
-    const int k = (int)(g / ((int64_t)n_cc * n_tb));
-    const int cols = 2 * N, c_base = cc * kCols;
-    const int64_t pub_row = (int64_t)cols * ES;         // bytes per public (a, k) row
-    uint8_t *held = (INGEST ? dst : const_cast<uint8_t *>(src)) + (int64_t)tb * lay.ts + (int64_t)k * lay.ks;
+// w[r]: 4 bytes of row r, elements of ES bytes -> w[i]: the 4 / ES rows of element
+// i.  Its own inverse.
+template <int ES>
+__device__ __forceinline__ void transpose(uint32_t *w) {
+    if constexpr (ES == 2) {
+        const uint32_t a = w[0], b = w[1];
+        w[0] = __builtin_amdgcn_perm(b, a, 0x05040100);
+        w[1] = __builtin_amdgcn_perm(b, a, 0x07060302);
+    } else if constexpr (ES == 1) {
+        const uint32_t a = __builtin_amdgcn_perm(w[1], w[0], 0x05010400);
+        const uint32_t b = __builtin_amdgcn_perm(w[1], w[0], 0x07030602);
+        const uint32_t c = __builtin_amdgcn_perm(w[3], w[2], 0x05010400);
+        const uint32_t d = __builtin_amdgcn_perm(w[3], w[2], 0x07030602);
+        w[0] = __builtin_amdgcn_perm(c, a, 0x05040100);
+        w[1] = __builtin_amdgcn_perm(c, a, 0x07060302);
+        w[2] = __builtin_amdgcn_perm(d, b, 0x05040100);
+        w[3] = __builtin_amdgcn_perm(d, b, 0x07060302);
+    }
+}
 
-    auto pub_addr = [&](int t, int col) -> int64_t {
-        return ((int64_t)(tb * TB + t) * C + k) * pub_row + (int64_t)col * ES;
+// INGEST: public src -> held dst (the tail of the last block zero-filled);
+// else held src -> public dst.  n_cols = channels moved x 2N; pub_row: bytes
+// between spectra of the public side.  Public vectors may lie at any multiple of
+// ES (a channel slice begins anywhere); the last one of a row may be part of 16
+// bytes.  SAT8 (int8 ingest): -128 is read as -127, the symmetric range the
+// X-engine's exact negation and the int32 overflow bound assume.
+template <typename T, bool INGEST, bool SAT8 = false>
+__global__ __launch_bounds__(kThreads) void relayout_kernel(const uint8_t *__restrict__ src,
+                                                             uint8_t *__restrict__ dst, uint32_t n_cols, uint32_t cols,
+                                                             int64_t pub_row, int n_spectra, int n_ct, bool blocks_first,
+                                                             SpecLayout lay, UserScale us) {
+    constexpr int ES = (int)sizeof(T), TB = kRowBytes / ES, VE = 16 / ES;
+    constexpr int RI = 4 / ES;                          // spectra of a dword
+    constexpr int CS = VE * 16 + 4;                     // LDS dwords of one vector's columns
+    __shared__ __align__(16) uint32_t lds[kCols / VE * CS];
+    const int n_tb = gridDim.x / n_ct;
+    const int tb = blocks_first ? blockIdx.x % n_tb : blockIdx.x / n_ct;
+    const uint32_t f0 = (uint32_t)(blocks_first ? blockIdx.x / n_tb : blockIdx.x % n_ct) * kCols;
+    const int tid = threadIdx.x, tg = tid / 64 * 4 + tid % 64 / 16;
+    const bool whole = f0 + kCols <= n_cols;            // no column past the end
+
+    // thread's public vectors: spectra a0 + r < n_spectra, r < RI; columns
+    // f0 + (16 q + tid % 16) VE, q < ES
+    const int a0 = tb * TB + tg * RI;
+    auto first_col = [&](int q) -> uint32_t { return f0 + (uint32_t)(q * 16 + tid % 16) * VE; };
+    auto pub_addr = [&](int r, uint32_t col) -> int64_t { return (int64_t)(a0 + r) * pub_row + (int64_t)col * ES; };
+    auto word = [&](int q, int i) -> uint32_t & { return lds[(q * 16 + tid % 16) * CS + i * 16 + tg]; };
+    auto held_rows = [&](auto &&move) {
+#pragma unroll
+        for (int it = 0; it < kCols * 4 / kThreads; ++it) {
+            const int j = it * (kThreads / 4) + tid / 4, hv = tid % 4;
+            const uint32_t f = f0 + j;
+            if (f >= n_cols) continue;
+            const uint32_t k = f / cols, col = f - k * cols;
+            move(lds + j / VE * CS + j % VE * 16 + hv * 4,
+                 (int64_t)tb * lay.ts + (int64_t)k * lay.ks + (int64_t)col * kRowBytes + hv * 16);
+        }
     };
-    if (INGEST) {
+
+    uint32_t w[ES][4][RI];                              // [vector column][dword][spectrum]
+    if constexpr (INGEST) {
         if (us.scale2)
-            for (int64_t c = g * kThreads + threadIdx.x; c < us.C; c += (int64_t)gridDim.x * kThreads)
+            for (int64_t c = (int64_t)blockIdx.x * kThreads + tid; c < us.C; c += (int64_t)gridDim.x * kThreads)
                 us.scale2[c] = us.inv ? square_of_scale(us.inv[c]) : 1.0f;
-        for (int i = threadIdx.x; i < PUB_VECS; i += kThreads) {
-            const int t = i / (W / 16), c = i % (W / 16);
-            const int a = tb * TB + t, col0 = c_base + c * VE;
-            uint4 v = make_uint4(0, 0, 0, 0);
-            if (a < n_spectra && col0 < cols) {
-                if (VEC && col0 + VE <= cols) {
-                    v = *reinterpret_cast<const uint4 *>(src + pub_addr(t, col0));
-                } else {
-                    T e[VE];
-                    for (int u = 0; u < VE; ++u)
-                        e[u] = col0 + u < cols ? *reinterpret_cast<const T *>(src + pub_addr(t, col0 + u)) : T(0);
-                    __builtin_memcpy(&v, e, 16);
+        uint4 v[ES][RI];
+        if (whole) {
+#pragma unroll
+            for (int q = 0; q < ES; ++q)
+#pragma unroll
+                for (int r = 0; r < RI; ++r) {
+                    // past the last spectrum: any row of the block that there is
+                    const int64_t o = a0 + r < n_spectra ? pub_addr(r, first_col(q))
+                                                         : (int64_t)tb * TB * pub_row + (int64_t)first_col(q) * ES;
+                    __builtin_memcpy(&v[q][r], src + o, 16);
+                }
+        } else {
+#pragma unroll
+            for (int q = 0; q < ES; ++q)
+#pragma unroll
+                for (int r = 0; r < RI; ++r) {
+                    const uint32_t col = first_col(q);
+                    v[q][r] = make_uint4(0, 0, 0, 0);
+                    if (a0 + r >= n_spectra) continue;
+                    if (col + VE <= n_cols) {
+                        __builtin_memcpy(&v[q][r], src + pub_addr(r, col), 16);
+                    } else {
+                        T e[VE];
+                        for (int u = 0; u < VE; ++u)
+                            e[u] = col + u < n_cols ? *reinterpret_cast<const T *>(src + pub_addr(r, col + u)) : T(0);
+                        __builtin_memcpy(&v[q][r], e, 16);
+                    }
+                }
+        }
+#pragma unroll
+        for (int q = 0; q < ES; ++q) {
+#pragma unroll
+            for (int r = 0; r < RI; ++r) {
+                uint32_t x[4] = {v[q][r].x, v[q][r].y, v[q][r].z, v[q][r].w};
+#pragma unroll
+                for (int d = 0; d < 4; ++d) {
+                    if constexpr (SAT8) x[d] = sat_int8x4(x[d]);
+                    w[q][d][r] = a0 + r < n_spectra ? x[d] : 0;
                 }
             }
-            if constexpr (SAT8) {
-                v.x = sat_int8x4(v.x);
-                v.y = sat_int8x4(v.y);
-                v.z = sat_int8x4(v.z);
-                v.w = sat_int8x4(v.w);
+#pragma unroll
+            for (int d = 0; d < 4; ++d) {
+                transpose<ES>(w[q][d]);
+#pragma unroll
+                for (int i = 0; i < RI; ++i) word(q, d * RI + i) = w[q][d][i];
             }
-            *reinterpret_cast<uint4 *>(lds + lds_elem<T>(t, c * VE)) = v;
         }
         __syncthreads();
-        for (int i = threadIdx.x; i < kCols * 4; i += kThreads) {
-            const int j = i >> 2, hv = i & 3, col = c_base + j;
-            if (col >= cols) continue;
-            T e[VE];
-            for (int u = 0; u < VE; ++u) e[u] = *reinterpret_cast<const T *>(lds + lds_elem<T>(hv * VE + u, j));
-            uint4 v;
-            __builtin_memcpy(&v, e, 16);
-            *reinterpret_cast<uint4 *>(held + (int64_t)col * kRowBytes + hv * 16) = v;
-        }
+        held_rows([&](const uint32_t *l, int64_t o) {
+            *reinterpret_cast<uint4 *>(dst + o) = *reinterpret_cast<const uint4 *>(l);
+        });
     } else {
-        for (int i = threadIdx.x; i < kCols * 4; i += kThreads) {
-            const int j = i >> 2, hv = i & 3, col = c_base + j;
-            if (col >= cols) continue;
-            const uint4 v = *reinterpret_cast<const uint4 *>(held + (int64_t)col * kRowBytes + hv * 16);
-            T e[VE];
-            __builtin_memcpy(e, &v, 16);
-            for (int u = 0; u < VE; ++u) *reinterpret_cast<T *>(lds + lds_elem<T>(hv * VE + u, j)) = e[u];
-        }
+        held_rows([&](uint32_t *l, int64_t o) {
+            *reinterpret_cast<uint4 *>(l) = *reinterpret_cast<const uint4 *>(src + o);
+        });
         __syncthreads();
-        for (int i = threadIdx.x; i < PUB_VECS; i += kThreads) {
-            const int t = i / (W / 16), c = i % (W / 16);
-            const int a = tb * TB + t, col0 = c_base + c * VE;
-            if (a >= n_spectra || col0 >= cols) continue;
-            const uint4 v = *reinterpret_cast<const uint4 *>(lds + lds_elem<T>(t, c * VE));
-            if (VEC && col0 + VE <= cols) {
-                *reinterpret_cast<uint4 *>(dst + pub_addr(t, col0)) = v;
-            } else {
-                T e[VE];
-                __builtin_memcpy(e, &v, 16);
-                for (int u = 0; u < VE && col0 + u < cols; ++u)
-                    *reinterpret_cast<T *>(dst + pub_addr(t, col0 + u)) = e[u];
+#pragma unroll
+        for (int q = 0; q < ES; ++q) {
+            const uint32_t col = first_col(q);
+            if (col >= n_cols) continue;
+#pragma unroll
+            for (int d = 0; d < 4; ++d) {
+#pragma unroll
+                for (int i = 0; i < RI; ++i) w[q][d][i] = word(q, d * RI + i);
+                transpose<ES>(w[q][d]);
+            }
+#pragma unroll
+            for (int r = 0; r < RI; ++r) {
+                if (a0 + r >= n_spectra) continue;
+                const uint4 v = make_uint4(w[q][0][r], w[q][1][r], w[q][2][r], w[q][3][r]);
+                if (whole || col + VE <= n_cols) {
+                    __builtin_memcpy(dst + pub_addr(r, col), &v, 16);
+                } else {
+                    T e[VE];
+                    __builtin_memcpy(e, &v, 16);
+                    for (int u = 0; u < VE && col + u < n_cols; ++u)
+                        *reinterpret_cast<T *>(dst + pub_addr(r, col + u)) = e[u];
+                }
             }
         }
     }
@@ -266,20 +326,23 @@ hipError_t relayout_t(int C, int N, int n_spectra, SpecLayout lay, const void *s
                       hipStream_t s, int nk = -1) {
     constexpr int TB = kRowBytes / (int)sizeof(T);
     const int n_tb = (n_spectra + TB - 1) / TB;
-    const int n_cc = (2 * N + kCols - 1) / kCols;
-    const int64_t grid = (int64_t)(nk < 0 ? C : nk) * n_tb * n_cc;
+    const uint32_t cols = 2 * (uint32_t)N;
+    const int64_t n_cols = (int64_t)(nk < 0 ? C : nk) * cols, n_ct = (n_cols + kCols - 1) / kCols;
+    const int64_t grid = n_ct * n_tb;
     if (grid < 1) return hipSuccess;
-    if (grid > 0x7fffffffLL) return hipErrorInvalidConfiguration;
-    const void *pub = INGEST ? src : dst;
-    const bool vec = (2 * N * (int)sizeof(T)) % 16 == 0 && reinterpret_cast<uintptr_t>(pub) % 16 == 0;
-    const uint8_t *in = static_cast<const uint8_t *>(src);
-    uint8_t *out = static_cast<uint8_t *>(dst);
-    if (vec)
-        hipLaunchKernelGGL((relayout_kernel<T, INGEST, true, SAT8>), dim3((unsigned)grid), dim3(kThreads), 0, s, in,
-                           out, C, N, n_spectra, n_tb, n_cc, lay, us);
-    else
-        hipLaunchKernelGGL((relayout_kernel<T, INGEST, false, SAT8>), dim3((unsigned)grid), dim3(kThreads), 0, s, in,
-                           out, C, N, n_spectra, n_tb, n_cc, lay, us);
+    if (grid > 0x7fffffffLL || n_cols > 0xffffffffLL - kCols) return hipErrorInvalidConfiguration;
+    // Neighbouring workgroups take neighbouring columns, or, where a spectrum's
+    // columns are 1 MB and more, the time blocks of the same columns (ingest and
+    // export: 300 inputs x 1024 channels x 1000 FP16, 1.2 MB, 449 and 486 us, by
+    // columns 469 and 477; 512 x 1024 x 512 FP8, 1 MB, 200 and 205, 207 and 219;
+    // 512 x 2048 x 128 FP16, 4 MB, 210 and 204, 222 and 222; but 48 x 256 x 512 int8,
+    // 24 KB, 11.5 and 5.9, 9.4 and 6.7; 256 x 256 x 500 FP32, 512 KB, 84.9 and 104,
+    // 83.0 and 102).
+    const bool blocks_first = n_cols * (int)sizeof(T) >= 1 << 20;
+    hipLaunchKernelGGL((relayout_kernel<T, INGEST, SAT8>), dim3((unsigned)grid), dim3(kThreads), 0, s,
+                       static_cast<const uint8_t *>(src), static_cast<uint8_t *>(dst), (uint32_t)n_cols, cols,
+                       (int64_t)C * cols * (int)sizeof(T), n_spectra, (int)n_ct, blocks_first,
+                       lay, us);
     return hipGetLastError();
 }
 
