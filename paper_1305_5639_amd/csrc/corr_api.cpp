@@ -180,6 +180,19 @@ int default_tile(int N, int C) { return default_tile(tri_blocks(N, 64), tri_bloc
 
 int effective_tile(const corr_ctx *h) { return h->tile ? h->tile : default_tile(h->N, h->C); }
 
+// For a member of a persistent batched launch, whose fellow members fill the chip:
+// as above but for the number of blocks (24 sub-arrays of 129 to 256 inputs x 256
+// to 1024 channels, 128-input blocks everywhere and by this rule: FP16 2.17 / 2.10
+// ms, FP8 1.40 / 1.34, FP32 11.5 / 9.5), and in the low-precision forms, which are
+// near the memory bound there, 128-input blocks wherever one holds all inputs, for
+// the spectra are then read once and not twice (65 to 128 inputs, 64- and 128-input
+// blocks: FP16 1.00 / 0.88 ms, FP8 0.62 / 0.56, int8 0.575 / 0.565; FP32 4.1 / 4.6).
+int batch_tile(const corr_ctx *h) {
+    if (h->tile) return h->tile;
+    const int64_t n64 = tri_blocks(h->N, 64), n128 = tri_blocks(h->N, 128);
+    return (n128 == 1 && n64 > 1 && h->prec != P_FP32) || 5 * n64 >= 16 * n128 ? 128 : 64;
+}
+
 // For ni rows against nj columns.
 int rect_tile(const corr_ctx *h, int ni, int nj) {
     if (h->tile) return h->tile;
@@ -1109,8 +1122,9 @@ corr_status corr_xengine_batched(corr_batch_handle b, const int32_t *n_spectra) 
             direct.push_back(i);
             continue;
         }
+        const int bt = batch_tile(h);
         const int64_t n_tb = (n_spectra[i] + h->TB - 1) / h->TB;
-        order[t == 64 ? 0 : 1].push_back({n_tb * t * t, i});
+        order[bt == 64 ? 0 : 1].push_back({n_tb * bt * bt, i});
     }
     hipError_t e;
     for (int i : direct) {
@@ -1144,7 +1158,7 @@ corr_status corr_xengine_batched(corr_batch_handle b, const int32_t *n_spectra) 
             x.N = h->N;
             x.n_tb = (ns + h->TB - 1) / h->TB;
             x.tv = ns - (x.n_tb - 1) * h->TB;
-            x.tile = effective_tile(h);
+            x.tile = batch_tile(h);
             const int nb = (h->N + x.tile - 1) / x.tile;
             x.n_tiles = nb * (nb + 1) / 2;
             x.first_call = 0;
