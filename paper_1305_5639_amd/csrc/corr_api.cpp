@@ -157,18 +157,35 @@ bool default_dump(const corr_params *p) { return p->layout == CORR_TRI_LOWER && 
 bool aligned(const void *ptr, size_t a) { return ((uintptr_t)ptr % a) == 0; }
 
 // Default block size when none was set or tuned, given the blocks of 64 and of
-// 128 inputs that cover one channel.  128-input blocks reuse each operand more
+// 128 inputs that cover one channel and whether the inputs fill three quarters of
+// the latter's rows.  128-input blocks reuse each operand more
 // (1024 inputs x 512 channels x 1024 spectra, 64- against 128-input blocks: FP32
-// 13.7 / 11.4 ms, FP16 2.72 / 2.25, FP8 1.55 / 1.20), but only where they are
-// about as full (at least 3.2 64-input blocks for each: 300 inputs x 512 channels
-// int8, 2.5 for each, 104 / 145 us) and enough for every CU to hold its two all
-// the time: a 64-input block ends sooner (256 inputs x 128 channels FP32, 384
-// blocks of 128: 55 / 67 us; x 512, 1536 blocks: 218 / 205 us; 512 inputs x 256
-// channels int8, 2560: 131 / 146 us; x 512, 5120: 334 / 287 us).  Against the
-// better of both at 137 shapes of 65..1024 inputs x 16..2048 channels, each of 3,
-// 12 and 40 time blocks, the rule loses 0.2% to 1.3% on average, depending on
-// form and length.
-int default_tile(int64_t n64, int64_t n128, int C) { return 5 * n64 >= 16 * n128 && C * n128 >= 2000 ? 128 : 64; }
+// 13.7 / 11.4 ms, FP16 2.72 / 2.25, FP8 1.55 / 1.20); a 64-input block ends sooner.
+//  - FP32: 128 where they are about as full (at least 3.2 64-input blocks for each)
+//    and enough for every CU to hold its two all the time (256 inputs x 128
+//    channels, 384 blocks of 128: 55 / 67 us; x 512, 1536 blocks: 218 / 205 us).
+//  - The low-precision forms: by how often the blocks fill the chip, which holds
+//    1024 of 64 inputs or 512 of 128.  A last filling that is not whole counts as
+//    three quarters of its share and one quarter whole, less than one as one, and a
+//    filling of 128-input blocks as 1.5 of 64-input ones, or 1.45 where their rows
+//    are full (300 inputs x 512 channels int8, 7.5 and 6 fillings: 104 / 145 us; 512
+//    x 256, 9 and 5: 131 / 146; x 512, 18 and 10: 334 / 287; 96 inputs x 512
+//    channels x 2560 spectra, 1.5 and 1: 54 / 44; x 2048, 6 and 4: 246 / 221; but 80
+//    inputs x 2048 x 768 FP8: 1.39 times slower in 128-input blocks).
+// Against the better of both at 137 shapes of 65..1024 inputs x 16..2048 channels,
+// each of 3, 12 and 40 time blocks, the rule loses 0.2% to 1.3% on average in FP32,
+// 0.6% to 2.1% in the others, depending on form and length.
+int default_tile(int prec, int64_t n64, int64_t n128, bool full, int C) {
+    if (prec == P_FP32) return 5 * n64 >= 16 * n128 && C * n128 >= 2000 ? 128 : 64;
+    auto fillings = [&](int64_t blocks, int64_t held) {   // in quarters of 1 / held
+        const int64_t whole = (blocks + held - 1) / held * held;
+        return blocks < held ? 4 * held : 3 * blocks + whole;
+    };
+    // fillings(64) / 1024 > 1.45 or 1.5 fillings(128) / 512
+    return 10 * fillings(C * n64, 1024) > (full ? 29 : 30) * fillings(C * n128, 512) ? 128 : 64;
+}
+
+bool fills_128(int n) { return 4 * (int64_t)n >= 3 * 128 * ((n + (int64_t)127) / 128); }
 
 int64_t tri_blocks(int N, int tile) {
     const int64_t n = (N + tile - 1) / tile;
@@ -176,12 +193,14 @@ int64_t tri_blocks(int N, int tile) {
 }
 
 // For the triangle of N inputs.
-int default_tile(int N, int C) { return default_tile(tri_blocks(N, 64), tri_blocks(N, 128), C); }
+int default_tile(int prec, int N, int C) {
+    return default_tile(prec, tri_blocks(N, 64), tri_blocks(N, 128), fills_128(N), C);
+}
 
-int effective_tile(const corr_ctx *h) { return h->tile ? h->tile : default_tile(h->N, h->C); }
+int effective_tile(const corr_ctx *h) { return h->tile ? h->tile : default_tile(h->prec, h->N, h->C); }
 
 // For a member of a persistent batched launch, whose fellow members fill the chip:
-// as above but for the number of blocks (24 sub-arrays of 129 to 256 inputs x 256
+// 128-input blocks where they are about as full (24 sub-arrays of 129 to 256 inputs x 256
 // to 1024 channels, 128-input blocks everywhere and by this rule: FP16 2.17 / 2.10
 // ms, FP8 1.40 / 1.34, FP32 11.5 / 9.5), and in the low-precision forms, which are
 // near the memory bound there, 128-input blocks wherever one holds all inputs, for
@@ -197,7 +216,7 @@ int batch_tile(const corr_ctx *h) {
 int rect_tile(const corr_ctx *h, int ni, int nj) {
     if (h->tile) return h->tile;
     auto blocks = [&](int64_t t) { return ((ni + t - 1) / t) * ((nj + t - 1) / t); };
-    return default_tile(blocks(64), blocks(128), h->C);
+    return default_tile(h->prec, blocks(64), blocks(128), fills_128(ni) && fills_128(nj), h->C);
 }
 
 const float *x_scale(const corr_ctx *h) {
@@ -820,7 +839,7 @@ corr_status corr_autotune(corr_handle h, int32_t n_spectra, int32_t *tile_out) {
     }
     const int Ct = tune_channels(h);
     const int cand[2] = {64, 128};
-    const int def_tile = default_tile(h->N, h->C);
+    const int def_tile = default_tile(h->prec, h->N, h->C);
     float best_ms = 0, def_ms = 0;
     int best = 0;
     {
@@ -895,7 +914,7 @@ corr_status corr_autotune_fx(corr_handle h, const void *d_volts, int64_t ld_samp
 
     const int n_tb = (n_spectra + h->TB - 1) / h->TB;
     const bool def_tb = default_tb_major(h->C, h->N, elem_bytes(h->prec));
-    const int def_tile = default_tile(h->N, h->C);
+    const int def_tile = default_tile(h->prec, h->N, h->C);
     const TuneKey key{h->arch, 1, h->prec, (h->N + 63) / 64, h->C, n_tb, 0};
     TuneVal best{def_tile, def_tb ? 1 : 0};
     float best_ms = 0, def_ms = 0;
@@ -1305,7 +1324,7 @@ corr_status corr_xengine_noalloc(const corr_params *params, const void *d_spectr
                                    UserScale{d_inv_scale, scaled && k0 == 0 ? s2 : nullptr, C}, stream);
         if (e != hipSuccess) return hip_fail(nullptr, e, "ingest launch");
         uint8_t *vis = static_cast<uint8_t *>(d_vis) + (int64_t)k0 * B * 8;
-        e = launch_xengine(prec, default_tile(N, n), n, N, n_spectra, spec, lay, scaled ? s2 + k0 : nullptr, vis, vis,
+        e = launch_xengine(prec, default_tile(prec, N, n), n, N, n_spectra, spec, lay, scaled ? s2 + k0 : nullptr, vis, vis,
                            accumulate ? 0 : 1, stream);
         if (e != hipSuccess) return hip_fail(nullptr, e, "xengine launch");
     }
