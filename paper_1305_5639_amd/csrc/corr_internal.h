@@ -68,6 +68,14 @@ inline int64_t spec_buffer_bytes(int C, int N, int n_tb_cap, int elem) {
     return most;
 }
 
+// Which entries k < C of a per-channel table thread tid of workgroup w writes, of
+// n_work workgroups of th threads: f(k) for each.  In 64 bits: n_work th passes 2^31
+// where a call has 2^36 values (512 inputs x 1024 channels x 131072 spectra).
+template <typename F>
+__host__ __device__ inline void for_share(int w, int n_work, int th, int tid, int C, F f) {
+    for (int64_t k = (int64_t)w * th + tid; k < C; k += (int64_t)n_work * th) f((int)k);
+}
+
 #ifdef __HIP__
 // s_k^2 = 1 / inv_s[k]^2
 __device__ __forceinline__ float square_of_scale(float inv) { return (float)(1.0 / ((double)inv * (double)inv)); }

@@ -669,8 +669,7 @@ __global__ __launch_bounds__((threads<C, PREC, REAL>())) __attribute__((amdgpu_w
     if (w >= n_work) return;
     // the X-engine's s_k^2, written here rather than by a launch of its own
     // (2 us of each call: 16-station F + X 21.8 -> 20.3 us)
-    if (scale2)
-        for (int k = w * TH + tid; k < C; k += n_work * TH) scale2[k] = square_of_scale(inv_scale[k]);
+    if (scale2) for_share(w, n_work, TH, tid, C, [&](int k) { scale2[k] = square_of_scale(inv_scale[k]); });
     const int rest = w / GPT;
     const int p = rest % N;
     const int a0 = ((rest / N) * GPT + w % GPT) * T;
