@@ -238,14 +238,20 @@ __device__ __forceinline__ void wave_stage(Acc (&re)[FR][FC], Acc (&im)[FR][FC],
 // A float32 is the exact sum of three BF16 values (8 significand bits each,
 // rounded to nearest, so the parts carry signs and all 24 bits are held).  Of
 // the nine products of two such sums the six largest are formed; what is left
-// out is below 2^-25 of the product, with either sign.  Six 32x32x16 BF16 MFMAs
-// (8 passes each) stand in for eight 32x32x2 FP32 ones (16 passes each).
+// out is at most 2^-24 of the product (2^-24.01 of x * x at x = 1.0038986, above
+// 2^-25 for 2% of all significands), and has one sign where the inputs do not
+// change.  Six 32x32x16 BF16 MFMAs (8 passes each) stand in for eight 32x32x2 FP32
+// ones (16 passes each).
 // Bound: the matrix cores' BF16 rate under the power limit (1024 inputs x 512
 // channels x 1024 spectra: 16.6 ms = 132 TFLOP/s with FP32 MFMAs, 11.6 ms = 190
 // TFLOP/s split, which is 1140 TFLOP/s of BF16 products; the BF16 library
 // product reaches 1158 on this card).  Error against 64 bits, relative to the
-// triangle's norm, same shape: 6.2e-7 with FP32 MFMAs, 1.5e-7 split (16 spectra:
-// 9.8e-8 and 6.8e-8).
+// triangle's norm, with FP32 MFMAs and split, 130 inputs x 64 channels x
+// 1024 spectra (4096; long_tile below): noise 6.2e-7 and 1.6e-7 (1.2e-6 and 1.5e-7),
+// a source common to all inputs, in quadrature, 6.0e-7 and 2.9e-7 (1.2e-6 and
+// 2.9e-7), a tone without noise 6.3e-7 and 4.4e-7 (1.3e-6 and 7.5e-7), constant inputs
+// 1.1e-5 and 2.2e-6 (4.2e-5 and 3.9e-6).  The gain is in the sums; a product alone (the other spectra zero) is rounded once
+// by an FP32 MFMA, and up to twice as far off here.
 //
 // The matrix cores take BF16 values and products below the normal range as
 // zero, an error of 2^-126 in each of A * 24 products.  That is nothing beside
@@ -298,9 +304,10 @@ __device__ __forceinline__ void mfma_bf16(f32x16 &c, i32x4 a, i32x4 b) {
 // real sums take a stage's 16 spectra from zero, smallest products first, and
 // are added to the running ones on the vector ALU: with the products going
 // straight into the running sums the autos, which only grow, lost accuracy
-// (1024 spectra: 1.3e-6 against 6.2e-7 with FP32 MFMAs); the imaginary sums,
-// which have no such terms, did not, and go straight in.  a1 is negated in
-// place for the products that enter with a minus sign.
+// (1024 spectra: 1.3e-6 against 6.2e-7 with FP32 MFMAs).  The imaginary sums go
+// straight in: inputs in quadrature make them grow like autos, and they then lie
+// between (1024 spectra: 2.8e-7 rms, real sums 7.7e-8, FP32 MFMAs 4.3e-7).  a1 is
+// negated in place for the products that enter with a minus sign.
 template <int FR, int FC, bool TRI = false, typename Acc>
 __device__ __forceinline__ void wave_stage_split(Acc (&re)[FR][FC], Acc (&im)[FR][FC], const uint8_t *smem, int a,
                                                  int b, float (&most)[FR + FC]) {
@@ -681,6 +688,36 @@ __device__ __forceinline__ void tile(uint8_t *smem, const uint8_t *__restrict__ 
     }
 }
 
+// The same in calls longer than kSegment time blocks, FP32: piece by piece, each
+// added to the sums in memory.  Running float sums take a rounding error per time
+// block, and where the blocks bring nearly the same (a tone without noise) those
+// errors have one sign: they grow with the blocks that one running sum takes
+// (such tones, 130 inputs, error relative to the triangle's norm with FP32 MFMAs, in
+// one piece and in pieces: 8192 spectra 1.8e-6, 2.9e-6, 7e-7; 2048, one piece, 8.8e-7
+// and 8.0e-7).  A piece costs one more pass over the block's sums: 512 inputs x 512
+// channels x 2048 spectra 6.4 ms, one piece; 256 x 1024 x 4096 7.54 ms either way.
+constexpr int kSegment = 128;
+template <int PREC, int TILE, bool RECT = false>
+__device__ __forceinline__ void long_tile(uint8_t *smem, const uint8_t *__restrict__ base_k, int64_t t_stride, int N,
+                                          int n_tb, int tv, int I0, int J0, int k, const float *__restrict__ scale2,
+                                          void *__restrict__ acc_out, const void *acc_in, int64_t B, int first_call,
+                                          int tid, OutMap om = OutMap{}) {
+    if constexpr (PREC != P_FP32) {
+        tile<PREC, TILE, RECT>(smem, base_k, t_stride, N, n_tb, tv, I0, J0, k, scale2, acc_out, acc_in, B, first_call,
+                               tid, om);
+    } else {
+        for (int t0 = 0; t0 < n_tb; t0 += kSegment) {
+            if (t0) __syncthreads();                   // every wave is done with smem
+            int t = tid;
+            asm volatile("" : "+v"(t));                // (the block's addresses are not kept across pieces)
+            const bool last = n_tb - t0 <= kSegment;
+            tile<PREC, TILE, RECT>(smem, base_k + (int64_t)t0 * t_stride, t_stride, N, last ? n_tb - t0 : kSegment,
+                                   last ? tv : kRowBytes / 4, I0, J0, k, scale2, acc_out, t0 ? acc_out : acc_in, B,
+                                   t0 ? 0 : first_call, t, om);
+        }
+    }
+}
+
 // Lower-triangle block t of a tiling with blocks (bi, bj), bj <= bi, in the
 // order (0,0), (1,0), (1,1), (2,0), ...
 __device__ __forceinline__ void tri_block(int t, int &bi, int &bj) {
@@ -709,8 +746,8 @@ __global__ __launch_bounds__((WaveGrid<PREC, TILE>::THREADS)) __attribute__((amd
     bi = uniform(bi);
     bj = uniform(bj);
     const int fc = zflag && *zflag ? 1 : first_call;
-    tile<PREC, TILE>(smem, spec + (int64_t)k * k_stride, t_stride, N, n_tb, tv, bi * TILE, bj * TILE, k, scale2,
-                     acc_out, acc_in, B, fc, threadIdx.x);
+    long_tile<PREC, TILE>(smem, spec + (int64_t)k * k_stride, t_stride, N, n_tb, tv, bi * TILE, bj * TILE, k, scale2,
+                          acc_out, acc_in, B, fc, threadIdx.x);
 }
 
 // Small arrays, N <= 32 NB inputs (NB = 1, or 2 for FP32): one workgroup per channel,
@@ -897,9 +934,9 @@ __global__ __launch_bounds__((WaveGrid<PREC, TILE>::THREADS)) __attribute__((amd
     if (w >= n_work) return;
     const int nb = nbi * nbj;
     const int k = uniform(w / nb), bi = uniform((w % nb) / nbj), bj = uniform(w % nbj);
-    tile<PREC, TILE, true>(smem, spec + (int64_t)k * k_stride, t_stride, N, n_tb, tv, om.r0 + bi * TILE,
-                           om.c0 + bj * TILE, k,
-                           scale2, out, out, B, first_call, threadIdx.x, om);
+    long_tile<PREC, TILE, true>(smem, spec + (int64_t)k * k_stride, t_stride, N, n_tb, tv, om.r0 + bi * TILE,
+                                om.c0 + bj * TILE, k,
+                                scale2, out, out, B, first_call, threadIdx.x, om);
 }
 
 // Persistent X-engine over many sub-arrays with blocks of TILE inputs, so
@@ -955,17 +992,19 @@ __global__ __launch_bounds__((WaveGrid<PREC, TILE>::THREADS)) __attribute__((amd
             }
             const XDesc &d = desc[cur];
             const int64_t local = item - d.qbegin[x];
-            const int k = x * d.C / kXcds + (int)(local / d.n_tiles);
+            const int k = uniform(x * d.C / kXcds + (int)(local / d.n_tiles));
             int bi, bj;
             tri_block((int)(local % d.n_tiles), bi, bj);
+            bi = uniform(bi);
+            bj = uniform(bj);
             // an opaque copy of the thread index keeps the block body's
             // per-lane address arithmetic inside the loop instead of live
             // across it (which cost registers and occupancy)
             int t = tid;
             asm volatile("" : "+v"(t));
-            tile<PREC, TILE>(smem, d.spec + (int64_t)k * d.k_stride, d.tb_stride, d.N, d.n_tb, d.tv, bi * TILE,
-                             bj * TILE, k,
-                             d.scale2, d.acc, d.acc, d.B, cur_fc, t);
+            long_tile<PREC, TILE>(smem, d.spec + (int64_t)k * d.k_stride, d.tb_stride, d.N, d.n_tb, d.tv, bi * TILE,
+                                  bj * TILE, k,
+                                  d.scale2, d.acc, d.acc, d.B, cur_fc, t);
             if (tid == 0) s_item = next;
             __syncthreads();                            // also: every wave is done with smem
             item = (unsigned int)__builtin_amdgcn_readfirstlane((int)s_item);
@@ -1011,10 +1050,20 @@ hipError_t launch_small(int C, int N, int n_spectra, const void *spec, SpecLayou
     const int n_tb = (n_spectra + TB - 1) / TB;
     const int tv = n_spectra - (n_tb - 1) * TB;
     if (n_tb <= 0 || C <= 0 || N < 1 || N > 32 * NB) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((xengine_small_kernel<PREC, NB>), dim3((C + 7) / 8 * 8), dim3(SmallGrid<NB>::THREADS), 0, stream,
-                       static_cast<const uint8_t *>(spec), N, C, n_tb, tv, lay.ks, lay.ts, scale2, acc, acc_in,
-                       (int64_t)N * (N + 1) / 2, first_call, zflag);
-    return hipGetLastError();
+    // FP32: in pieces like long_tile(), kSegment time blocks to a wave, each a launch
+    // (in one launch their loop cost the kernel 4%: 20 inputs x 1024 channels x 4096
+    // spectra 0.182 -> 0.189 ms)
+    const int piece = PREC == P_FP32 ? kSegment * SmallGrid<NB>::KS : n_tb;
+    for (int t0 = 0; t0 < n_tb; t0 += piece) {
+        const bool last = n_tb - t0 <= piece;
+        hipLaunchKernelGGL((xengine_small_kernel<PREC, NB>), dim3((C + 7) / 8 * 8), dim3(SmallGrid<NB>::THREADS), 0,
+                           stream, static_cast<const uint8_t *>(spec) + t0 * lay.ts, N, C, last ? n_tb - t0 : piece,
+                           last ? tv : TB, lay.ks, lay.ts, scale2, acc, t0 ? acc : acc_in, (int64_t)N * (N + 1) / 2,
+                           t0 ? 0 : first_call, t0 ? nullptr : zflag);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 template <int PREC>
