@@ -854,22 +854,18 @@ __global__ __launch_bounds__((SmallGrid<NB>::THREADS)) __attribute__((amdgpu_wav
         }
     };
     if constexpr (PREC == P_FP32) {                    // (the rules of tile())
-        bool plain = n_tb == 1 && tail;
-        if (!plain) {
-            sum(std::true_type{});
-            float bad = 0.0f;
+        sum(std::true_type{});
+        float bad = 0.0f;
 #pragma unroll
-            for (int f = 0; f < NB; ++f)
+        for (int f = 0; f < NB; ++f)
 #pragma unroll
-                for (int c = 0; c <= f; ++c)
+            for (int c = 0; c <= f; ++c)
 #pragma unroll
-                    for (int r = 0; r < 16; ++r) bad += 0.0f * re[f][c][r] + 0.0f * im[f][c][r];
+                for (int r = 0; r < 16; ++r) bad += 0.0f * re[f][c][r] + 0.0f * im[f][c][r];
 #pragma unroll
-            for (int i = 0; i < NB; ++i)
-                if (most[i] != 0.0f && most[i] < kLeast) bad = 1.0f;
-            plain = __syncthreads_or(bad != 0.0f);
-        }
-        if (plain) sum(std::false_type{});
+        for (int i = 0; i < NB; ++i)
+            if (most[i] != 0.0f && most[i] < kLeast) bad = 1.0f;
+        if (__syncthreads_or(bad != 0.0f)) sum(std::false_type{});
     } else {
         sum(std::false_type{});
     }
