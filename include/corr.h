@@ -62,6 +62,15 @@ typedef enum {
 
 /* Arithmetic forms of the X-engine input (the F-engine requantises into it).
  *   CORR_FP32     : float32 spectra, float32 accumulation.
+ *                   Products are formed on the BF16 matrix cores from three
+ *                   parts of each value.  Spectra that these do not carry --
+ *                   an input whose largest value in a call is below 2^-40
+ *                   and not 0, values above 2^127, infinities, NaN, sums
+ *                   past the float range -- are summed with FP32
+ *                   instructions instead, as accurately but slower (1.3 to 1.6
+ *                   times in calls where all inputs are that small, up to
+ *                   twice where a first such value appears late): scale
+ *                   data in very small physical units up.
  *   CORR_FP16     : IEEE binary16 spectra (round half to even, saturating at
  *                   +-65504), float32 accumulation.
  *   CORR_FP8_E4M3 : OCP FP8 E4M3 spectra (round half to even, saturating at

@@ -68,8 +68,9 @@ constexpr int kRB = 2 * kRowBytes;                     // LDS row bytes
 constexpr int kCPP = kRowBytes / 16;                   // 16-byte chunks per plane
 constexpr int kNT = 2;                                 // chunks per lane fragment
 __device__ __forceinline__ int swz(int r) { return (r >> 1) & 7; }
-// LDS of a block: two ring slots of 2 TILE rows.
+// LDS of a block: two ring slots of 2 TILE rows, and for FP32 a word (16 bytes).
 constexpr int ring_bytes(int tile) { return 2 * 2 * tile * kRB; }
+constexpr int lds_bytes(int prec, int tile) { return ring_bytes(tile) + (prec == P_FP32 ? 16 : 0); }
 
 // Per-precision fragment type and MFMA step for NT chunks per lane.  A
 // fragment feeds NSUB MFMAs (sub-step e of the fragment).  The same chunk to
@@ -256,8 +257,17 @@ __device__ __forceinline__ void wave_stage(Acc (&re)[FR][FC], Acc (&im)[FR][FC],
 // The matrix cores take BF16 values and products below the normal range as
 // zero, an error of 2^-126 in each of A * 24 products.  That is nothing beside
 // sqrt(C_ii C_jj) where both inputs have a value of at least kLeast (2^-40) in the
-// integration, or are zero.
-constexpr float kLeast = 0x1p-40f;
+// integration, or are zero.  Values above kMost have no finite parts.
+constexpr float kLeast = 0x1p-40f, kMost = 0x1p127f;
+// A block with a value or a sum that the split does not carry is summed again, with
+// FP32 MFMAs.  The values are looked at every kLook time blocks, from the first on,
+// and the split ends there (512 inputs x 512 channels x 1024 spectra, all values small
+// 7.3 -> 4.8 ms, one input small 5.4 -> 3.9, an infinity in the middle 5.4 -> 4.7; usual
+// data 3.0 either way, and with FP32 MFMAs in blocks of 64 alone 4.4).
+constexpr int kLook = 16;
+__device__ __forceinline__ bool unfit(float most) {
+    return !(most <= kMost) || (most != 0.0f && most < kLeast);
+}
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 struct Split {
@@ -272,13 +282,14 @@ __device__ __forceinline__ f32x8 load8(const uint8_t *p, int o) {
     return f32x8{a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
 }
 
-// The same, split; most: their largest magnitude so far.
+// The same, split; most: their largest magnitude so far, NaN once there is one.
 __device__ __forceinline__ Split split8(f32x8 v, float &most) {
     Split s;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         float x = v[2 * i], y = v[2 * i + 1];
-        most = __builtin_fmaxf(__builtin_fmaxf(most, __builtin_fabsf(x)), __builtin_fabsf(y));
+        most = __builtin_elementwise_maximum(__builtin_elementwise_maximum(most, __builtin_fabsf(x)),
+                                             __builtin_fabsf(y));
 #pragma unroll
         for (int q = 0; q < 3; ++q) {
             const bf16x2 h{(__bf16)x, (__bf16)y};
@@ -495,9 +506,20 @@ __device__ __forceinline__ void tile(uint8_t *smem, const uint8_t *__restrict__ 
     const uint8_t *pb0 = smem + (diag ? 0 : OPB) + (wj * QC + m) * RB;
     const bool tail = tv < TB;
 
-    // The sums over all stages; SPLIT (FP32): on the BF16 matrix cores.
+    // (FP32) set where a wave has met a value that the split does not carry
+    int *const stop = reinterpret_cast<int *>(smem + ring_bytes(TILE));
+    auto met_unfit = [&] {
+        bool b = false;
+#pragma unroll
+        for (int i = 0; i < FR + FC; ++i) b |= unfit(most[i]);
+        return b;
+    };
+
+    // The sums over all stages; SPLIT (FP32): on the BF16 matrix cores, up to a value
+    // that they do not carry.
     auto sum = [&](auto split) {
         constexpr bool SPLIT = decltype(split)::value;
+        if (SPLIT && tid == 0) *stop = 0;              // (written again after the first barrier only)
 #pragma unroll
         for (int f = 0; f < FR; ++f)
 #pragma unroll
@@ -513,6 +535,7 @@ __device__ __forceinline__ void tile(uint8_t *smem, const uint8_t *__restrict__ 
         for (int t = 0; t < S; ++t) {
             wait_vm<0>();                               // this wave's copies of block t landed
             __syncthreads();                            // block t landed; the other slot is free
+            if (SPLIT && t % kLook == 1 && uniform(*stop)) break;
             // The copies go out at a raised wave priority, ahead of the MFMAs of
             // the other waves on the SIMD (the first block's copies too: a
             // further 0.2-1%; the FP16, FP8 and int8 forms otherwise
@@ -532,7 +555,8 @@ __device__ __forceinline__ void tile(uint8_t *smem, const uint8_t *__restrict__ 
                 asm volatile("" : "+v"(x));            // (rebuilt, not kept: see issue)
                 const int row = x & 31, w = x >> 6, chunk = 16 * ((x >> 5 & 1) * NT ^ swz(row));
                 wave_stage_split<FR, FC>(re, im, smem + so, (w / WC * QS + row) * RB + chunk,
-                                              (diag ? 0 : OPB) + (w % WC * QC + row) * RB + chunk, most);
+                                         (diag ? 0 : OPB) + (w % WC * QC + row) * RB + chunk, most);
+                if (t % kLook == 0 && met_unfit()) *stop = 1;
             } else if constexpr (PREC == P_FP32) {
                 wave_stage<PREC, FR, FC, 0>(re, im, pa0 + so, pb0 + so, off);
             } else {
@@ -547,12 +571,12 @@ __device__ __forceinline__ void tile(uint8_t *smem, const uint8_t *__restrict__ 
         // Under one whole block of spectra there are too few roundings for the
         // split to gain accuracy (1 to 3 spectra: 5e-8 against 3e-8 to 5e-8
         // relative), and little to do: FP32 MFMAs.  They also sum a block
-        // again where the split met values it cannot carry: an input's too small
-        // (see kLeast), or one that left a sum that is not finite.
+        // again where the split met a value it cannot carry (see kLeast), or left
+        // a sum that is not finite.
         bool plain = S == 1 && tail;
         if (!plain) {
             sum(std::true_type{});
-            float bad = 0.0f;
+            float bad = met_unfit() ? 1.0f : 0.0f;
             if (active) {
 #pragma unroll
                 for (int f = 0; f < FR; ++f)
@@ -561,9 +585,6 @@ __device__ __forceinline__ void tile(uint8_t *smem, const uint8_t *__restrict__ 
 #pragma unroll
                         for (int r = 0; r < 16; ++r) bad += 0.0f * re[f][c][r] + 0.0f * im[f][c][r];
             }
-            #pragma unroll
-            for (int i = 0; i < FR + FC; ++i)
-                if (most[i] != 0.0f && most[i] < kLeast) bad = 1.0f;
             plain = __syncthreads_or(bad != 0.0f);
         }
         if (plain) sum(std::false_type{});
@@ -736,7 +757,7 @@ __global__ __launch_bounds__((WaveGrid<PREC, TILE>::THREADS)) __attribute__((amd
     const uint8_t *__restrict__ spec, int N, int n_tiles, int n_work, int n_tb, int tv,
     int64_t k_stride, int64_t t_stride, const float *__restrict__ scale2, void *__restrict__ acc_out,
     const void *acc_in, int64_t B, int first_call, const int *__restrict__ zflag) {
-    __shared__ __attribute__((aligned(16))) uint8_t smem[ring_bytes(TILE)];
+    __shared__ __attribute__((aligned(16))) uint8_t smem[lds_bytes(PREC, TILE)];
     const int per = (n_work + 7) / 8;
     const int w = (blockIdx.x % 8) * per + blockIdx.x / 8;
     if (w >= n_work) return;
@@ -821,6 +842,12 @@ __global__ __launch_bounds__((SmallGrid<NB>::THREADS)) __attribute__((amdgpu_wav
     const bool tail = tv < kRowBytes / ES;
     Acc re[NB][NB], im[NB][NB];
     float most[2 * NB] = {};
+    auto met_unfit = [&] {
+        bool b = false;
+#pragma unroll
+        for (int i = 0; i < NB; ++i) b |= unfit(most[i]);
+        return b;
+    };
     auto sum = [&](auto split) {
 #pragma unroll
         for (int f = 0; f < NB; ++f)
@@ -847,24 +874,29 @@ __global__ __launch_bounds__((SmallGrid<NB>::THREADS)) __attribute__((amdgpu_wav
                 asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
             }
             const uint8_t *p = ring + (i & 1) * STG + m * kRB;
-            if constexpr (decltype(split)::value)
+            if constexpr (decltype(split)::value) {
                 wave_stage_split<NB, NB, true>(re, im, p, off[0][0], off[0][0], most);
-            else
+                // each wave sees all inputs: no word to the others (with two blocks or
+                // less there is little to end: 33 inputs x 512 channels x 64 spectra 11.2
+                // us, looking 11.5)
+                if (n > 2 && i % kLook == 0 && __any(met_unfit())) {
+                    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                    break;
+                }
+            } else {
                 wave_stage<PREC, NB, NB, 0, true>(re, im, p, p, off);
+            }
         }
     };
     if constexpr (PREC == P_FP32) {                    // (the rules of tile())
         sum(std::true_type{});
-        float bad = 0.0f;
+        float bad = met_unfit() ? 1.0f : 0.0f;
 #pragma unroll
         for (int f = 0; f < NB; ++f)
 #pragma unroll
             for (int c = 0; c <= f; ++c)
 #pragma unroll
                 for (int r = 0; r < 16; ++r) bad += 0.0f * re[f][c][r] + 0.0f * im[f][c][r];
-#pragma unroll
-        for (int i = 0; i < NB; ++i)
-            if (most[i] != 0.0f && most[i] < kLeast) bad = 1.0f;
         if (__syncthreads_or(bad != 0.0f)) sum(std::false_type{});
     } else {
         sum(std::false_type{});
@@ -924,7 +956,7 @@ template <int PREC, int TILE>
 __global__ __launch_bounds__((WaveGrid<PREC, TILE>::THREADS)) __attribute__((amdgpu_waves_per_eu((WaveGrid<PREC, TILE>::EU)))) void xengine_rect_kernel(
     const uint8_t *__restrict__ spec, int N, int nbi, int nbj, int n_work, int n_tb, int tv, int64_t k_stride,
     int64_t t_stride, const float *__restrict__ scale2, void *__restrict__ out, int64_t B, int first_call, OutMap om) {
-    __shared__ __attribute__((aligned(16))) uint8_t smem[ring_bytes(TILE)];
+    __shared__ __attribute__((aligned(16))) uint8_t smem[lds_bytes(PREC, TILE)];
     const int per = (n_work + 7) / 8;
     const int w = (blockIdx.x % 8) * per + blockIdx.x / 8;
     if (w >= n_work) return;
@@ -948,7 +980,7 @@ __global__ __launch_bounds__((WaveGrid<PREC, TILE>::THREADS)) __attribute__((amd
 template <int PREC, int TILE>
 __global__ __launch_bounds__((WaveGrid<PREC, TILE>::THREADS)) __attribute__((amdgpu_waves_per_eu((WaveGrid<PREC, TILE>::EU)))) void xengine_batched_kernel(
     const XQueue *__restrict__ plan, const XDesc *__restrict__ all_desc, unsigned int *__restrict__ counter) {
-    __shared__ __attribute__((aligned(16))) uint8_t smem[ring_bytes(TILE)];
+    __shared__ __attribute__((aligned(16))) uint8_t smem[lds_bytes(PREC, TILE)];
     __shared__ unsigned int s_item;
     const int tid = threadIdx.x;
     const int n_desc = plan->n_desc;

@@ -110,3 +110,28 @@ def test_values_without_parts(way, N, value, spectrum):
         im = sign * float(value) * S[spectrum][:, other, 1].astype(np.float64)
         for part, w in ((got.real[:, rows], re), (got.imag[:, rows], im)):
             assert np.allclose(part, w, rtol=2.0 ** -22, atol=0, equal_nan=True)
+
+
+def test_small_inputs_end_the_split_early():
+    """Where the second sum is known to be needed from the first time block on, the
+    first one ends there: both in full take more than twice as long as usual
+    data, the second alone 1.4 times."""
+    N, C, A = 128, 2048, 512
+    say(f"fp32 time of small inputs N={N} C={C} A={A}")
+    S = torch.empty((A, C, N, 2), device=DEV).normal_(generator=torch.Generator(device=DEV).manual_seed(13))
+    times = []
+    for scale in (1.0, 2.0 ** -46):
+        with corr.Correlator(N, 1, C, A, "fp32") as c:
+            c.xengine(A, S * scale)
+            out = c.new_visibilities()
+            t = []
+            for _ in range(9):
+                e = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+                e[0].record()
+                c.xengine_dump(A, out)
+                e[1].record()
+                torch.cuda.synchronize()
+                t.append(e[0].elapsed_time(e[1]))
+            times.append(sorted(t)[4])
+    say(f"  {times[0]:.3f} and {times[1]:.3f} ms")
+    assert times[1] < 1.75 * times[0]
