@@ -859,7 +859,7 @@ __global__ __launch_bounds__((SmallGrid<NB>::THREADS)) __attribute__((amdgpu_wav
                     im[f][c][r] = 0;
                 }
         if (n > 0) issue(0);
-        for (int i = 0; i < n; ++i) {
+        auto block = [&](int i) {
             // the slot's last reads are done; the next block goes out before
             // this one is waited for
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
@@ -874,30 +874,43 @@ __global__ __launch_bounds__((SmallGrid<NB>::THREADS)) __attribute__((amdgpu_wav
                 asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
             }
             const uint8_t *p = ring + (i & 1) * STG + m * kRB;
-            if constexpr (decltype(split)::value) {
+            if constexpr (decltype(split)::value)
                 wave_stage_split<NB, NB, true>(re, im, p, off[0][0], off[0][0], most);
-                // each wave sees all inputs: no word to the others (with two blocks or
-                // less there is little to end: 33 inputs x 512 channels x 64 spectra 11.2
-                // us, looking 11.5)
-                if (n > 2 && i % kLook == 0 && __any(met_unfit())) {
-                    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            else
+                wave_stage<PREC, NB, NB, 0, true>(re, im, p, p, off);
+        };
+        if constexpr (decltype(split)::value) {
+            // The values are looked at once, after two blocks, and by each wave for
+            // itself: it sees all inputs.  Not where looking shows and there is little to
+            // end: 16 inputs x 64 channels x 1024 spectra, 8 blocks a wave, F + X 18.2 ->
+            // 18.3 us, and 20 x 4096 x 1024 small values 472 us without, usual data 188;
+            // 48 x 4096 x 512, 8 blocks of a larger triangle, 711 without and 522.
+            for (int i = 0, end = n > (NB == 1 ? 8 : 4) ? 2 : n;; end = n) {
+                for (; i < end; ++i) block(i);
+                if (end == n) break;
+                if (__any(met_unfit())) {
+                    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // (the block on its way)
                     break;
                 }
-            } else {
-                wave_stage<PREC, NB, NB, 0, true>(re, im, p, p, off);
             }
+        } else {
+            for (int i = 0; i < n; ++i) block(i);
         }
     };
     if constexpr (PREC == P_FP32) {                    // (the rules of tile())
-        sum(std::true_type{});
-        float bad = met_unfit() ? 1.0f : 0.0f;
+        bool plain = n_tb == 1 && tail;                // (the last piece of a long call may be that)
+        if (!plain) {
+            sum(std::true_type{});
+            float bad = met_unfit() ? 1.0f : 0.0f;
 #pragma unroll
-        for (int f = 0; f < NB; ++f)
+            for (int f = 0; f < NB; ++f)
 #pragma unroll
-            for (int c = 0; c <= f; ++c)
+                for (int c = 0; c <= f; ++c)
 #pragma unroll
-                for (int r = 0; r < 16; ++r) bad += 0.0f * re[f][c][r] + 0.0f * im[f][c][r];
-        if (__syncthreads_or(bad != 0.0f)) sum(std::false_type{});
+                    for (int r = 0; r < 16; ++r) bad += 0.0f * re[f][c][r] + 0.0f * im[f][c][r];
+            plain = __syncthreads_or(bad != 0.0f);
+        }
+        if (plain) sum(std::false_type{});
     } else {
         sum(std::false_type{});
     }
