@@ -338,7 +338,8 @@ CORR_API corr_status corr_set_tile(corr_handle h, int32_t tile);
  * to *tile (may be NULL).  Results are cached per (device architecture,
  * precision, inputs rounded up to 64, channels, time blocks, spectra order)
  * for the process, and in the text file named by the environment variable
- * CORR_TUNE_CACHE when it is set.  Synchronises the stream; CORR_E_STATE
+ * CORR_TUNE_CACHE when it is set (its lines name the kernels' revision; those
+ * of another one are ignored).  Synchronises the stream; CORR_E_STATE
  * while the stream is being captured into a graph.
  */
 CORR_API corr_status corr_autotune(corr_handle h, int32_t n_spectra, int32_t *tile);

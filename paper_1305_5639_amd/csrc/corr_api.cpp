@@ -230,9 +230,13 @@ const float *x_scale(const corr_ctx *h) {
 // blocks timed and (for the X-engine-only tuner) the spectra order; value:
 // the block size and, for the F + X tuner, the spectra order.  Kept for the
 // process and, when CORR_TUNE_CACHE names a file, appended to it as lines
-//   fx <arch> <prec> <N/64> <C> <n_tb> <tile> <tb_major>
-//   x  <arch> <prec> <N/64> <C> <n_tb> <tb_major> <tile>
-// (other lines are ignored).
+//   fx2 <arch> <prec> <N/64> <C> <n_tb> <tile> <tb_major>
+//   x2  <arch> <prec> <N/64> <C> <n_tb> <tb_major> <tile>
+// (other lines are ignored).  The digit is the revision of the kernels that were
+// timed, raised with a change that moves the choice between block sizes: lines of
+// another one say nothing of these (the first revision's, without a digit, chose 64
+// for FP32 by FP32 MFMAs, where 128 is now up to 1.2 times faster).
+#define CORR_TUNE_REVISION "2"
 struct TuneKey {
     std::string arch;
     int kind, prec, nb, C, n_tb, order;       // kind 0: X-engine only, 1: F + X
@@ -258,9 +262,9 @@ void tune_load_locked() {
     while (std::fgets(line, sizeof line, f)) {
         int p, nb, C, nt, v1, v2;
         if (std::sscanf(line, "%7s %127s %d %d %d %d %d %d", kind, arch, &p, &nb, &C, &nt, &v1, &v2) != 8) continue;
-        if (!std::strcmp(kind, "fx") && (v1 == 64 || v1 == 128) && (v2 == 0 || v2 == 1))
+        if (!std::strcmp(kind, "fx" CORR_TUNE_REVISION) && (v1 == 64 || v1 == 128) && (v2 == 0 || v2 == 1))
             g_tune[{arch, 1, p, nb, C, nt, 0}] = {v1, v2};
-        else if (!std::strcmp(kind, "x") && (v1 == 0 || v1 == 1) && (v2 == 64 || v2 == 128))
+        else if (!std::strcmp(kind, "x" CORR_TUNE_REVISION) && (v1 == 0 || v1 == 1) && (v2 == 64 || v2 == 128))
             g_tune[{arch, 0, p, nb, C, nt, v1}] = {v2, v1};
     }
     std::fclose(f);
@@ -273,9 +277,9 @@ void tune_store_locked(const TuneKey &k, TuneVal v) {
     FILE *f = std::fopen(path, "a");
     if (!f) return;
     if (k.kind == 1)
-        std::fprintf(f, "fx %s %d %d %d %d %d %d\n", k.arch.c_str(), k.prec, k.nb, k.C, k.n_tb, v.tile, v.tb_major);
+        std::fprintf(f, "fx" CORR_TUNE_REVISION " %s %d %d %d %d %d %d\n", k.arch.c_str(), k.prec, k.nb, k.C, k.n_tb, v.tile, v.tb_major);
     else
-        std::fprintf(f, "x %s %d %d %d %d %d %d\n", k.arch.c_str(), k.prec, k.nb, k.C, k.n_tb, k.order, v.tile);
+        std::fprintf(f, "x" CORR_TUNE_REVISION " %s %d %d %d %d %d %d\n", k.arch.c_str(), k.prec, k.nb, k.C, k.n_tb, k.order, v.tile);
     std::fclose(f);
 }
 
@@ -293,8 +297,8 @@ int tune_channels(const corr_ctx *h) {
 // An autotuner replaces the built-in choice only by a candidate at least 2%
 // faster: the two block sizes often time within a percent of each other on
 // the channel subset, and which wins there need not win on all channels
-// (1024 inputs x 4096 FP32 channels: 64-input blocks 137.1-137.5 ms, 128-input
-// blocks 137.7-138.1 ms in full, the reverse on 256 channels).
+// (64- and 128-input blocks: FP16 192 inputs x 2048 channels x 1280 spectra 680
+// and 677 us, 320 x 1024 x 1280 722 and 716; int8 320 x 2048 x 768 534 and 538).
 constexpr float kTuneMargin = 0.98f;
 
 // Timing events and a scratch buffer owned by an autotuner call.
