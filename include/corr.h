@@ -336,8 +336,8 @@ CORR_API corr_status corr_set_tile(corr_handle h, int32_t tile);
  * this handle (the built-in choice unless another is at least 2% faster)
  * and write it
  * to *tile (may be NULL).  Results are cached per (device architecture,
- * precision, inputs rounded up to 64, channels, time blocks, spectra order)
- * for the process, and in the text file named by the environment variable
+ * precision, inputs rounded up to 64 (to 32 below that), channels, time
+ * blocks, spectra order) for the process, and in the text file named by the environment variable
  * CORR_TUNE_CACHE when it is set (its lines name the kernels' revision; those
  * of another one are ignored).  Synchronises the stream; CORR_E_STATE
  * while the stream is being captured into a graph.
@@ -374,8 +374,8 @@ typedef struct {
  * chosen order, so the handle then holds their spectra as after
  * corr_fengine (the accumulators are not touched).  Arguments as for
  * corr_fengine (n_spectra <= n_integrate).  Results are cached per (device
- * architecture, precision, inputs rounded up to 64, channels, time blocks)
- * for the process and in the file named by CORR_TUNE_CACHE when set.
+ * architecture, precision, inputs rounded up to 64 (to 32 below that),
+ * channels, time blocks) for the process and in the file named by CORR_TUNE_CACHE when set.
  * Synchronises the stream; CORR_E_STATE while capturing and for batch
  * sub-arrays.  *out (may be NULL) receives the choice and both timings.  The
  * spectra held before the call are dropped (on an error, none are held).

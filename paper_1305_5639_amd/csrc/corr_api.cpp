@@ -226,12 +226,13 @@ const float *x_scale(const corr_ctx *h) {
 }
 
 // Autotune cache.  Key: the device's architecture name, the precision, the
-// inputs rounded up to 64 (the smaller block size), the channels, the time
-// blocks timed and (for the X-engine-only tuner) the spectra order; value:
+// inputs rounded up to 64 (the smaller block size; 0 for up to 32, which the
+// small-array kernel takes in every form and 33 to 64 in FP32 only), the channels,
+// the time blocks timed and (for the X-engine-only tuner) the spectra order; value:
 // the block size and, for the F + X tuner, the spectra order.  Kept for the
 // process and, when CORR_TUNE_CACHE names a file, appended to it as lines
-//   fx2 <arch> <prec> <N/64> <C> <n_tb> <tile> <tb_major>
-//   x2  <arch> <prec> <N/64> <C> <n_tb> <tb_major> <tile>
+//   fx2 <arch> <prec> <nb> <C> <n_tb> <tile> <tb_major>
+//   x2  <arch> <prec> <nb> <C> <n_tb> <tb_major> <tile>
 // (other lines are ignored).  The digit is the revision of the kernels that were
 // timed, raised with a change that moves the choice between block sizes: lines of
 // another one say nothing of these (the first revision's, without a digit, chose 64
@@ -244,6 +245,7 @@ struct TuneKey {
         return std::tie(arch, kind, prec, nb, C, n_tb, order) < std::tie(o.arch, o.kind, o.prec, o.nb, o.C, o.n_tb, o.order);
     }
 };
+int tune_inputs(int N) { return N <= 32 ? 0 : (N + 63) / 64; }
 struct TuneVal {
     int tile, tb_major;
 };
@@ -830,7 +832,7 @@ corr_status corr_autotune(corr_handle h, int32_t n_spectra, int32_t *tile_out) {
     if (e != hipSuccess) return hip_fail(h, e, "hipStreamIsCapturing");
     if (cs != hipStreamCaptureStatusNone) return fail(h, CORR_E_STATE, "cannot autotune while capturing");
     const int n_tb = (n_spectra + h->TB - 1) / h->TB;
-    const TuneKey key{h->arch, 0, h->prec, (h->N + 63) / 64, h->C, n_tb, h->tb_major ? 1 : 0};
+    const TuneKey key{h->arch, 0, h->prec, tune_inputs(h->N), h->C, n_tb, h->tb_major ? 1 : 0};
     {
         std::lock_guard<std::mutex> lk(g_tune_mu);
         tune_load_locked();
@@ -919,7 +921,7 @@ corr_status corr_autotune_fx(corr_handle h, const void *d_volts, int64_t ld_samp
     const int n_tb = (n_spectra + h->TB - 1) / h->TB;
     const bool def_tb = default_tb_major(h->C, h->N, elem_bytes(h->prec));
     const int def_tile = default_tile(h->prec, h->N, h->C);
-    const TuneKey key{h->arch, 1, h->prec, (h->N + 63) / 64, h->C, n_tb, 0};
+    const TuneKey key{h->arch, 1, h->prec, tune_inputs(h->N), h->C, n_tb, 0};
     TuneVal best{def_tile, def_tb ? 1 : 0};
     float best_ms = 0, def_ms = 0;
     bool cached = false;

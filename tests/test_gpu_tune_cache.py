@@ -45,3 +45,12 @@ def test_saved_choices(tmp_path):
     (_, timed), = tune(old, 100)
     assert timed
     assert old.read_text().splitlines()[-1].startswith("fx2 ")
+
+
+def test_one_choice_per_kernel(tmp_path):
+    """Up to 32 inputs another kernel runs in the low-precision forms than up to 64:
+    a choice timed at one says nothing of the other."""
+    say("autotuner cache: 20, 60, 31 and 33 inputs")
+    cache = tmp_path / "tune.txt"
+    assert [timed for _, timed in tune(cache, 20, 60, 31, 33)] == [True, True, False, False]
+    assert [l.split()[3] for l in cache.read_text().splitlines()] == ["0", "1"]
