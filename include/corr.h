@@ -320,9 +320,9 @@ CORR_API corr_status corr_get_counts(corr_handle h, int32_t *n_held, int64_t *n_
 /*
  * X-engine block size.  The triangle of each channel is covered by square
  * blocks of `tile` inputs (64 or 128); 0 selects a default unless
- * corr_autotune has chosen: 128 or 64 by a rule on how full such blocks are and
- * how they fill the GPU.  Larger blocks reuse each operand
- * more; smaller ones run more workgroups per CU and waste less on the diagonal
+ * corr_autotune has chosen: 128 or 64, for each call, by a rule on how full such
+ * blocks are, how they fill the GPU and how many spectra the call has.  Larger
+ * blocks reuse each operand more; smaller ones run more workgroups per CU and waste less on the diagonal
  * and on ragged N.  Results do not depend on it beyond the rounding of float
  * sums.
  */

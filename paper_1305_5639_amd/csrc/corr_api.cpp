@@ -156,33 +156,45 @@ bool default_dump(const corr_params *p) { return p->layout == CORR_TRI_LOWER && 
 
 bool aligned(const void *ptr, size_t a) { return ((uintptr_t)ptr % a) == 0; }
 
-// Default block size when none was set or tuned, given the blocks of 64 and of
-// 128 inputs that cover one channel and whether the inputs fill three quarters of
-// the latter's rows.  128-input blocks reuse each operand more
-// (1024 inputs x 512 channels x 1024 spectra, 64- against 128-input blocks: FP32
-// 13.7 / 11.4 ms, FP16 2.72 / 2.25, FP8 1.55 / 1.20); a 64-input block ends sooner.
-//  - FP32: 128 where they are about as full (at least 3.2 64-input blocks for each)
-//    and enough for every CU to hold its two all the time (256 inputs x 128
-//    channels, 384 blocks of 128: 55 / 67 us; x 512, 1536 blocks: 218 / 205 us).
-//  - The low-precision forms: by how often the blocks fill the chip, which holds
-//    1024 of 64 inputs or 512 of 128.  A last filling that is not whole counts as
-//    three quarters of its share and one quarter whole, less than one as one, and a
-//    filling of 128-input blocks as 1.5 of 64-input ones, or 1.45 where their rows
-//    are full (300 inputs x 512 channels int8, 7.5 and 6 fillings: 104 / 145 us; 512
-//    x 256, 9 and 5: 131 / 146; x 512, 18 and 10: 334 / 287; 96 inputs x 512
-//    channels x 2560 spectra, 1.5 and 1: 54 / 44; x 2048, 6 and 4: 246 / 221; but 80
-//    inputs x 2048 x 768 FP8: 1.39 times slower in 128-input blocks).
-// Against the better of both at 137 shapes of 65..1024 inputs x 16..2048 channels,
-// each of 3, 12 and 40 time blocks, the rule loses 0.2% to 1.3% on average in FP32,
-// 0.6% to 2.1% in the others, depending on form and length.
-int default_tile(int prec, int64_t n64, int64_t n128, bool full, int C) {
-    if (prec == P_FP32) return 5 * n64 >= 16 * n128 && C * n128 >= 2000 ? 128 : 64;
+// Default block size when none was set or tuned, given the blocks of 64 and of 128
+// inputs that cover the channels, whether the inputs fill three quarters of the
+// latter's rows, the time blocks and the CUs.  128-input blocks reuse each operand more
+// (64- against 128-input blocks, 512 inputs: FP32 x 256 channels x 1600 spectra 2.81 /
+// 2.46 ms, int8 x 512 x 768 0.35 / 0.29); 64-input blocks divide the work more finely and
+// cover less that is not asked for.  What counts is how often the blocks fill the chip,
+// which holds four of 64 inputs or two of 128 per CU.  128 where the fillings by
+// 64-input blocks are more than those by 128-input ones, times
+//  - FP32: 1.5 (256 inputs x 512 channels x 1600 spectra, 5 and 3 fillings: 1.56 / 1.46
+//    ms); in calls of up to 8 time blocks, where writing the sums counts for more, 1.8
+//    (200 x 2048 x 16, 20 and 12: 0.124 / 0.161).
+//  - FP16 and int8: 1.4 (300 inputs x 512 channels x 768 int8, 7.5 and 6: 112 / 139 us;
+//    256 x 128 x 384 FP16, 1.25 and 0.75: 30 / 25; 80 x 2048 x 2560 int8, 6 and 4: 231 /
+//    203).  Up to 8 time blocks 1.25 (320 x 256 x 192 FP16, 3.75 and 3: 61 / 49).
+//    With rows less full, whose empty part the waves of a 128-input block skip,
+//    1.5 up to 24 time blocks, and any up to 8 (80 x 512 x 192 FP8: 9.3 / 11.3).
+//  - FP8, whose blocks are the shortest: 1.25 up to 8 time blocks, then 1.6, and 1.7 from
+//    25 to 64 (200 x 128 x 2560, 1.25 and 0.75: 48 / 58; 200 x 256 x 2560, 2.5 and 1.5: 88
+//    / 104).  With rows less full any up to 64, then 1.6 (72 x 1024 x 2560, 3 and 2: 108 /
+//    124).
+// Less than one filling counts as one.  A last one that is not whole counts as three
+// quarters of its share and one quarter whole; by its share alone in long FP32 calls
+// (450 x 64 x 640, 2.25 and 1.25: 0.28 / 0.30 ms).  Against the better of both at 161
+// shapes of 65..1024 inputs x 16..2048 channels, each of 1 to 100 time blocks, the rule
+// loses 0.1% to 1.4% on average, depending on form and length, at worst 12% in FP32 and
+// 27% in the others (100 x 2048 x 192 int8, whose rows count as full).
+int default_tile(int prec, int64_t n64, int64_t n128, bool full, int n_tb, int cus) {
+    const bool brief = n_tb <= 8;
+    const int64_t held = 2 * cus;                         // 128-input blocks; 2 held of 64 inputs
     auto fillings = [&](int64_t blocks, int64_t held) {   // in quarters of 1 / held
-        const int64_t whole = (blocks + held - 1) / held * held;
-        return blocks < held ? 4 * held : 3 * blocks + whole;
+        if (blocks < held) return 4 * held;
+        return prec == P_FP32 && !brief ? 4 * blocks : 3 * blocks + (blocks + held - 1) / held * held;
     };
-    // fillings(64) / 1024 > 1.45 or 1.5 fillings(128) / 512
-    return 10 * fillings(C * n64, 1024) > (full ? 29 : 30) * fillings(C * n128, 512) ? 128 : 64;
+    int ratio;                                            // 20 times those above
+    if (prec == P_FP32) ratio = brief ? 36 : 30;
+    else if (full) ratio = brief ? 25 : prec != P_FP8 ? 28 : n_tb > 24 && n_tb <= 64 ? 34 : 32;
+    else if (prec == P_FP8) ratio = n_tb <= 64 ? 40 : 32;
+    else ratio = brief ? 40 : n_tb <= 24 ? 30 : 28;
+    return 10 * fillings(n64, 2 * held) > ratio * fillings(n128, held) ? 128 : 64;
 }
 
 bool fills_128(int n) { return 4 * (int64_t)n >= 3 * 128 * ((n + (int64_t)127) / 128); }
@@ -192,12 +204,15 @@ int64_t tri_blocks(int N, int tile) {
     return n * (n + 1) / 2;
 }
 
-// For the triangle of N inputs.
-int default_tile(int prec, int N, int C) {
-    return default_tile(prec, tri_blocks(N, 64), tri_blocks(N, 128), fills_128(N), C);
+// For the triangles of N inputs in C channels.
+int default_tile(int prec, int N, int C, int n_spectra, int cus) {
+    const int TB = time_block(prec);
+    return default_tile(prec, C * tri_blocks(N, 64), C * tri_blocks(N, 128), fills_128(N), (n_spectra + TB - 1) / TB, cus);
 }
 
-int effective_tile(const corr_ctx *h) { return h->tile ? h->tile : default_tile(h->prec, h->N, h->C); }
+int default_tile(const corr_ctx *h, int n_spectra) { return default_tile(h->prec, h->N, h->C, n_spectra, h->num_cus); }
+
+int effective_tile(const corr_ctx *h, int n_spectra) { return h->tile ? h->tile : default_tile(h, n_spectra); }
 
 // For a member of a persistent batched launch, whose fellow members fill the chip:
 // 128-input blocks where they are about as full (24 sub-arrays of 129 to 256 inputs x 256
@@ -213,10 +228,11 @@ int batch_tile(const corr_ctx *h) {
 }
 
 // For ni rows against nj columns.
-int rect_tile(const corr_ctx *h, int ni, int nj) {
+int rect_tile(const corr_ctx *h, int ni, int nj, int n_spectra) {
     if (h->tile) return h->tile;
-    auto blocks = [&](int64_t t) { return ((ni + t - 1) / t) * ((nj + t - 1) / t); };
-    return default_tile(h->prec, blocks(64), blocks(128), fills_128(ni) && fills_128(nj), h->C);
+    auto blocks = [&](int64_t t) { return h->C * ((ni + t - 1) / t) * ((nj + t - 1) / t); };
+    return default_tile(h->prec, blocks(64), blocks(128), fills_128(ni) && fills_128(nj), (n_spectra + h->TB - 1) / h->TB,
+                        h->num_cus);
 }
 
 const float *x_scale(const corr_ctx *h) {
@@ -608,7 +624,7 @@ corr_status corr_fx(corr_handle h, const void *d_volts, int64_t ld_samples, int3
                            d_inv_scale ? d_inv_scale : h->unit_scale, h->twiddle, h->spec, h->lay,
                            FScratch{h->gscr, h->gscr_bytes}, 0, h->scale2, h->stream);
         if (e != hipSuccess) return hip_fail(h, e, "fengine launch");
-        e = launch_xengine(h->prec, effective_tile(h), h->C, h->N, ns, h->spec, h->lay,
+        e = launch_xengine(h->prec, effective_tile(h, ns), h->C, h->N, ns, h->spec, h->lay,
                            h->prec == P_INT8 ? nullptr : h->scale2, h->acc, h->acc, h->acc_zero ? 1 : 0, h->stream);
         if (e != hipSuccess) return hip_fail(h, e, "xengine launch");
         h->acc_zero = false;
@@ -663,7 +679,7 @@ corr_status corr_xengine(corr_handle h, const void *d_spectra, int32_t n_spectra
     const float *s2 = nullptr;
     const corr_status st = prepare_x(h, d_spectra, n_spectra, d_inv_scale, &s2);
     if (st != CORR_OK) return st;
-    hipError_t e = launch_xengine(h->prec, effective_tile(h), h->C, h->N, n_spectra, h->spec, h->lay, s2, h->acc,
+    hipError_t e = launch_xengine(h->prec, effective_tile(h, n_spectra), h->C, h->N, n_spectra, h->spec, h->lay, s2, h->acc,
                                   h->acc, h->acc_zero ? 1 : 0, h->stream, h->zflag);
     if (e == hipSuccess && h->zflag) e = launch_set_flag(h->zflag, 0, h->stream);
     if (e != hipSuccess) return hip_fail(h, e, "xengine launch");
@@ -683,7 +699,7 @@ corr_status corr_xengine_dump(corr_handle h, const void *d_spectra, int32_t n_sp
     const float *s2 = nullptr;
     const corr_status st = prepare_x(h, d_spectra, n_spectra, d_inv_scale, &s2);
     if (st != CORR_OK) return st;
-    const hipError_t e = launch_xengine(h->prec, effective_tile(h), h->C, h->N, n_spectra, h->spec, h->lay, s2,
+    const hipError_t e = launch_xengine(h->prec, effective_tile(h, n_spectra), h->C, h->N, n_spectra, h->spec, h->lay, s2,
                                         d_dst, h->acc, h->acc_zero ? 1 : 0, h->stream);
     if (e != hipSuccess) return hip_fail(h, e, "xengine launch");
     h->acc_zero = true;                                  // the integration ends here: reset
@@ -706,7 +722,7 @@ corr_status corr_xengine_rect(corr_handle h, int32_t i0, int32_t ni, int32_t j0,
     if (n_spectra > h->n_held) return fail(h, CORR_E_STATE, "n_spectra exceeds the spectra held");
     if (h->prec == P_INT8 && n_spectra > CORR_INT8_MAX_INTEGRATE)
         return fail(h, CORR_E_OVERFLOW, "int8 rectangle over more than 66572 spectra");
-    const hipError_t e = launch_xengine_rect(h->prec, rect_tile(h, ni, nj), h->C, h->N, n_spectra, h->spec,
+    const hipError_t e = launch_xengine_rect(h->prec, rect_tile(h, ni, nj, n_spectra), h->C, h->N, n_spectra, h->spec,
                                              h->lay, x_scale(h), d_out, accumulate ? 0 : 1, i0, ni, j0, nj,
                                              h->stream);
     if (e != hipSuccess) return hip_fail(h, e, "rectangle launch");
@@ -845,7 +861,7 @@ corr_status corr_autotune(corr_handle h, int32_t n_spectra, int32_t *tile_out) {
     }
     const int Ct = tune_channels(h);
     const int cand[2] = {64, 128};
-    const int def_tile = default_tile(h->prec, h->N, h->C);
+    const int def_tile = default_tile(h, n_spectra);
     float best_ms = 0, def_ms = 0;
     int best = 0;
     {
@@ -920,7 +936,7 @@ corr_status corr_autotune_fx(corr_handle h, const void *d_volts, int64_t ld_samp
 
     const int n_tb = (n_spectra + h->TB - 1) / h->TB;
     const bool def_tb = default_tb_major(h->C, h->N, elem_bytes(h->prec));
-    const int def_tile = default_tile(h->prec, h->N, h->C);
+    const int def_tile = default_tile(h, n_spectra);
     const TuneKey key{h->arch, 1, h->prec, tune_inputs(h->N), h->C, n_tb, 0};
     TuneVal best{def_tile, def_tb ? 1 : 0};
     float best_ms = 0, def_ms = 0;
@@ -1139,7 +1155,7 @@ corr_status corr_xengine_batched(corr_batch_handle b, const int32_t *n_spectra) 
     for (int i = 0; i < n; ++i) {
         if (!n_spectra[i]) continue;
         const corr_ctx *h = b->subs[i];
-        const int t = effective_tile(h);
+        const int t = effective_tile(h, n_spectra[i]);
         const int64_t nb = (h->N + t - 1) / t;
         const int64_t items = (int64_t)h->C * (nb * (nb + 1) / 2);
         const int64_t resident = (int64_t)b->num_cus * (t == 64 ? 4 : 2);
@@ -1154,7 +1170,7 @@ corr_status corr_xengine_batched(corr_batch_handle b, const int32_t *n_spectra) 
     hipError_t e;
     for (int i : direct) {
         corr_ctx *h = b->subs[i];
-        e = launch_xengine(h->prec, effective_tile(h), h->C, h->N, n_spectra[i], h->spec, h->lay, x_scale(h), h->acc,
+        e = launch_xengine(h->prec, effective_tile(h, n_spectra[i]), h->C, h->N, n_spectra[i], h->spec, h->lay, x_scale(h), h->acc,
                            h->acc, 0, b->stream, h->zflag);
         if (e == hipSuccess) e = launch_set_flag(h->zflag, 0, b->stream);
         if (e != hipSuccess) return fail(nullptr, CORR_E_HIP, std::string("direct launch: ") + hipGetErrorString(e));
@@ -1258,10 +1274,11 @@ namespace {
 
 std::mutex g_scratch_mu;
 void *g_scratch_ptr[kNoAllocMaxDevices] = {};
+int g_scratch_cus[kNoAllocMaxDevices] = {};
 
 // The device address of `scratch` on the current device (taken once per
-// device); the array's name is only a host-side stand-in.
-hipError_t scratch_address(void **out) {
+// device); the array's name is only a host-side stand-in.  And the device's CUs.
+hipError_t scratch_address(void **out, int *cus) {
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return e;
@@ -1270,10 +1287,12 @@ hipError_t scratch_address(void **out) {
     if (!g_scratch_ptr[dev]) {
         void *p = nullptr;
         e = hipGetSymbolAddress(&p, HIP_SYMBOL(scratch));
+        if (e == hipSuccess) e = hipDeviceGetAttribute(&g_scratch_cus[dev], hipDeviceAttributeMultiprocessorCount, dev);
         if (e != hipSuccess) return e;
         g_scratch_ptr[dev] = p;
     }
     *out = g_scratch_ptr[dev];
+    *cus = g_scratch_cus[dev];
     return hipSuccess;
 }
 
@@ -1318,7 +1337,8 @@ corr_status corr_xengine_noalloc(const corr_params *params, const void *d_spectr
     // ---- HIP from here on ----
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     void *base = nullptr;
-    hipError_t e = scratch_address(&base);
+    int cus = 0;
+    hipError_t e = scratch_address(&base, &cus);
     if (e != hipSuccess) return hip_fail(nullptr, e, "hipGetSymbolAddress(scratch)");
     float *s2 = static_cast<float *>(base);
     uint8_t *spec = static_cast<uint8_t *>(base) + s2_bytes;
@@ -1330,7 +1350,7 @@ corr_status corr_xengine_noalloc(const corr_params *params, const void *d_spectr
                                    UserScale{d_inv_scale, scaled && k0 == 0 ? s2 : nullptr, C}, stream);
         if (e != hipSuccess) return hip_fail(nullptr, e, "ingest launch");
         uint8_t *vis = static_cast<uint8_t *>(d_vis) + (int64_t)k0 * B * 8;
-        e = launch_xengine(prec, default_tile(prec, N, n), n, N, n_spectra, spec, lay, scaled ? s2 + k0 : nullptr, vis, vis,
+        e = launch_xengine(prec, default_tile(prec, N, n, n_spectra, cus), n, N, n_spectra, spec, lay, scaled ? s2 + k0 : nullptr, vis, vis,
                            accumulate ? 0 : 1, stream);
         if (e != hipSuccess) return hip_fail(nullptr, e, "xengine launch");
     }
