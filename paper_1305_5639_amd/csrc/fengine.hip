@@ -71,12 +71,9 @@ constexpr int threads() {
 // 4-byte pieces; with the chunked store and gather used from 2048 channels
 // on, 32 (no spills) is faster at every size (4096 channels x 1024 inputs x
 // 1024 FP8: 16.2 -> 14.5 ms; 8192 x 256 x 128 int8: 1.53 -> 1.15 ms).  A
-// workgroup of TH threads transforms T = TH PT / C spectra; the helpers below
-// recover PT as T C / TH.
-template <int C, int PREC, bool REAL>
-constexpr int per_thread() {
-    return 32;
-}
+// workgroup of TH threads transforms T = TH kPT / C spectra; the helpers below
+// take T and TH.
+constexpr int kPT = 32;
 
 __device__ __forceinline__ float2 cadd(float2 a, float2 b) { return make_float2(a.x + b.x, a.y + b.y); }
 __device__ __forceinline__ float2 csub(float2 a, float2 b) { return make_float2(a.x - b.x, a.y - b.y); }
@@ -404,10 +401,10 @@ __device__ __forceinline__ void exchange(float2 *v, float *lds, int tid, bool wa
 // and how the real-input form finds the partner Z[C - k] of each Z[k]: in the
 // same thread (MAP_PAIRED, or C/R = 1 where every butterfly has j = 0), else
 // through LDS.
-template <int C, int PT = 32> struct Last {
+template <int C> struct Last {
     using P = Plan<C>;
     static constexpr int RL = P::NP == 1 ? P::R0 : (P::NP == 2 ? P::R1 : P::R2);
-    static constexpr int Q = PT / RL, CR = C / RL;
+    static constexpr int Q = kPT / RL, CR = C / RL;
     static constexpr bool PAIRED = CR >= 2 && Q % 2 == 0;
     static constexpr bool REAL_VIA_LDS = CR >= 2 && Q % 2 == 1;
 };
@@ -616,14 +613,14 @@ __device__ __forceinline__ uint32_t plane_word(const Words &w, const Pos &pos, i
 // never null (the host passes a table of ones for "no scale").
 template <int C, int PREC, bool REAL>
 __global__ __launch_bounds__((threads<C, PREC, REAL>())) __attribute__((amdgpu_waves_per_eu(
-    PREC == P_FP32 || (REAL && Last<C>::REAL_VIA_LDS) || per_thread<C, PREC, REAL>() == 64 ? 2 : 3))) void fengine_kernel(
+    PREC == P_FP32 || (REAL && Last<C>::REAL_VIA_LDS) ? 2 : 3))) void fengine_kernel(
     const void *__restrict__ in, int64_t ld, int N, int n_spectra, int n_valid_pad,
     int n_work, const float *__restrict__ inv_scale,
     const float2 *__restrict__ tw, const float2 *__restrict__ tw2, uint8_t *__restrict__ spec, int64_t k_stride,
     int64_t t_stride, int tb0, float *__restrict__ scale2) {
     using PR = Pair<PREC>;
     constexpr int TH = threads<C, PREC, REAL>();      // threads per workgroup
-    constexpr int PT = per_thread<C, PREC, REAL>();   // complex values per thread
+    constexpr int PT = kPT;
     constexpr int T = TH * PT / C;                     // spectra per workgroup
     using P = Plan<C>;
     static_assert(P::R0 * P::R1 * P::R2 == C, "radix plan must multiply to C");
@@ -798,7 +795,7 @@ hipError_t launch_c(int N, const void *in, int64_t ld, int n_spectra, const floa
                     const float2 *tw, const float2 *tw2, void *spec, SpecLayout lay, FScratch scr, int tb0,
                     float *scale2, hipStream_t stream) {
     constexpr int TH = threads<C, PREC, REAL>();
-    constexpr int T = TH * per_thread<C, PREC, REAL>() / C;
+    constexpr int T = TH * kPT / C;
     const int TB = time_block(PREC);
     const int n_tb = (n_spectra + TB - 1) / TB;
     auto run = [&](const void *src, int n_in, int ns, uint8_t *dst, int first_tb, float *s2) -> hipError_t {
