@@ -158,7 +158,8 @@ bool aligned(const void *ptr, size_t a) { return ((uintptr_t)ptr % a) == 0; }
 
 // Default block size when none was set or tuned, given the blocks of 64 and of 128
 // inputs that cover the channels, whether the inputs fill three quarters of the
-// latter's rows, the time blocks and the CUs.  128-input blocks reuse each operand more
+// latter's rows (a rectangle: nine sixteenths of their pairs), the time blocks and the
+// CUs.  128-input blocks reuse each operand more
 // (64- against 128-input blocks, 512 inputs: FP32 x 256 channels x 1600 spectra 2.81 /
 // 2.46 ms, int8 x 512 x 768 0.35 / 0.29); 64-input blocks divide the work more finely and
 // cover less that is not asked for.  What counts is how often the blocks fill the chip,
@@ -176,13 +177,17 @@ bool aligned(const void *ptr, size_t a) { return ((uintptr_t)ptr % a) == 0; }
 //    25 to 64 (200 x 128 x 2560, 1.25 and 0.75: 48 / 58; 200 x 256 x 2560, 2.5 and 1.5: 88
 //    / 104).  With rows less full any up to 64, then 1.6 (72 x 1024 x 2560, 3 and 2: 108 /
 //    124).
+//  - Low-precision rectangles, which have no half-empty blocks on a diagonal: 1.25 (268 x
+//    422 inputs x 32 channels x 1141 FP16, 1.1 and 0.75: 64 / 56), with blocks less full
+//    1.4 up to 64 time blocks (130 x 130 x 128 x 2304 FP8, 1.1 and 1: 46 / 50).
 // Less than one filling counts as one.  A last one that is not whole counts as three
 // quarters of its share and one quarter whole; by its share alone in long FP32 calls
 // (450 x 64 x 640, 2.25 and 1.25: 0.28 / 0.30 ms).  Against the better of both at 161
 // shapes of 65..1024 inputs x 16..2048 channels, each of 1 to 100 time blocks, the rule
 // loses 0.1% to 1.4% on average, depending on form and length, at worst 12% in FP32 and
-// 27% in the others (100 x 2048 x 192 int8, whose rows count as full).
-int default_tile(int prec, int64_t n64, int64_t n128, bool full, int n_tb, int cus) {
+// 27% in the others (100 x 2048 x 192 int8, whose rows count as full); at 112 rectangles
+// 0.2% to 0.9%, FP32 in one time block 2.4%, at worst 26%.
+int default_tile(int prec, bool rect, int64_t n64, int64_t n128, bool full, int n_tb, int cus) {
     const bool brief = n_tb <= 8;
     const int64_t held = 2 * cus;                         // 128-input blocks; 2 held of 64 inputs
     auto fillings = [&](int64_t blocks, int64_t held) {   // in quarters of 1 / held
@@ -191,6 +196,7 @@ int default_tile(int prec, int64_t n64, int64_t n128, bool full, int n_tb, int c
     };
     int ratio;                                            // 20 times those above
     if (prec == P_FP32) ratio = brief ? 36 : 30;
+    else if (rect) ratio = full || n_tb > 64 ? 25 : 28;
     else if (full) ratio = brief ? 25 : prec != P_FP8 ? 28 : n_tb > 24 && n_tb <= 64 ? 34 : 32;
     else if (prec == P_FP8) ratio = n_tb <= 64 ? 40 : 32;
     else ratio = brief ? 40 : n_tb <= 24 ? 30 : 28;
@@ -207,7 +213,7 @@ int64_t tri_blocks(int N, int tile) {
 // For the triangles of N inputs in C channels.
 int default_tile(int prec, int N, int C, int n_spectra, int cus) {
     const int TB = time_block(prec);
-    return default_tile(prec, C * tri_blocks(N, 64), C * tri_blocks(N, 128), fills_128(N), (n_spectra + TB - 1) / TB, cus);
+    return default_tile(prec, false, C * tri_blocks(N, 64), C * tri_blocks(N, 128), fills_128(N), (n_spectra + TB - 1) / TB, cus);
 }
 
 int default_tile(const corr_ctx *h, int n_spectra) { return default_tile(h->prec, h->N, h->C, n_spectra, h->num_cus); }
@@ -231,8 +237,8 @@ int batch_tile(const corr_ctx *h) {
 int rect_tile(const corr_ctx *h, int ni, int nj, int n_spectra) {
     if (h->tile) return h->tile;
     auto blocks = [&](int64_t t) { return h->C * ((ni + t - 1) / t) * ((nj + t - 1) / t); };
-    return default_tile(h->prec, blocks(64), blocks(128), fills_128(ni) && fills_128(nj), (n_spectra + h->TB - 1) / h->TB,
-                        h->num_cus);
+    const bool full = 16 * (int64_t)h->C * ni * nj >= 9 * 128 * 128 * blocks(128);
+    return default_tile(h->prec, true, blocks(64), blocks(128), full, (n_spectra + h->TB - 1) / h->TB, h->num_cus);
 }
 
 const float *x_scale(const corr_ctx *h) {
