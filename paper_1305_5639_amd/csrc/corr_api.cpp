@@ -178,8 +178,9 @@ bool aligned(const void *ptr, size_t a) { return ((uintptr_t)ptr % a) == 0; }
 //    / 104).  With rows less full any up to 64, then 1.6 (72 x 1024 x 2560, 3 and 2: 108 /
 //    124).
 //  - Low-precision rectangles, which have no half-empty blocks on a diagonal: 1.25 (268 x
-//    422 inputs x 32 channels x 1141 FP16, 1.1 and 0.75: 64 / 56), with blocks less full
-//    1.4 up to 64 time blocks (130 x 130 x 128 x 2304 FP8, 1.1 and 1: 46 / 50).
+//    422 of 700 inputs x 32 channels x 1141 FP16, 1.1 and 0.75, spectra not in the caches: 64
+//    / 56), with blocks less full 1.4 up to 64 time blocks (130 x 130 x 128 x 2304 FP8, 1.1
+//    and 1: 46 / 50).
 // Less than one filling counts as one.  A last one that is not whole counts as three
 // quarters of its share and one quarter whole; by its share alone in long FP32 calls
 // (450 x 64 x 640, 2.25 and 1.25: 0.28 / 0.30 ms).  Against the better of both at 161
